@@ -104,6 +104,8 @@ struct ags_model {
   std::vector<int> jtype;  // per link, to fill the limit margins at sim creation
   std::vector<unsigned long long> link_anc, col_anc;  // ancestor bit masks (links; generalized columns)
   std::vector<int> col_link;                           // owning link of each generalized column
+  std::vector<int> link_cols, jump;                    // dense step: columns moving a link, pointer-jumping table
+  int n_jump = 0;
   bool body_pairs = false;                             // has sphere/capsule-vs-box pairs
   int max_joint_entries = 0;  // most revolute/prismatic joints on the paths of one slot's two bodies
   std::vector<float> mass, com, inertia;
@@ -339,6 +341,27 @@ extern "C" int ags_model_create(const ags_actor_desc* actors, int32_t n_actors, 
       M->col_anc[own[a]] = m;
     }
   }
+  M->link_cols.assign(nl, 0);
+  M->jump.assign(nl, 0);
+  if (nl <= kDenseMaxLinks && ncol <= kDenseMaxV) {
+    for (int i = 0; i < nl; ++i)
+      for (int c = 0; c < ncol; ++c)
+        if ((M->link_anc[i] >> M->col_link[c]) & 1ull) M->link_cols[i] |= 1 << c;
+    std::vector<int> up(nl);
+    for (int i = 0; i < nl; ++i) up[i] = M->li[i * LI_COLS + LI_PARENT];
+    bool more = true;
+    for (int rd = 0; rd < 5; ++rd) {  // at most 32 links: five doublings reach every root
+      more = false;
+      std::vector<int> next(nl);
+      for (int i = 0; i < nl; ++i) {
+        more = more || up[i] >= 0;
+        M->jump[i] |= (up[i] >= 0 ? up[i] : 63) << (6 * rd);
+        next[i] = up[i] >= 0 ? up[up[i]] : -1;
+      }
+      if (more) M->n_jump = rd + 1;
+      up = next;
+    }
+  }
   // contact slots: plane pairs (sphere 1, capsule 2 caps, box 8 corners); box pairs (sphere 1, capsule 2 caps + midpoint)
   std::vector<std::vector<int>> body_entries(nl);
   int limited = 0;
@@ -461,6 +484,9 @@ struct TypeDev {
   int team = 64;
   DevModel dm{};
   Lds lds{};
+  bool dense = false;          // runs the dense step
+  DenseLds dl{};
+  size_t lds_bytes = 0;        // of a workgroup of its step
   void* block = nullptr;       // device tables
   int* env_list = nullptr;     // device env ids of this type
   // per-type launches with one environment per wavefront: the env ids in the order the next step dispatches
@@ -578,7 +604,7 @@ struct ags_sim {
   hipStream_t aux2 = nullptr;
   hipEvent_t ev_big_start = nullptr, ev_big_done = nullptr, ev_big_listed = nullptr;
   // persistent (fused) launch
-  bool fused_ok = false;
+  bool fused_ok = false, fused_dense = false;
   int* units = nullptr;  // device: (type, group) pairs
   int n_units = 0, fused_grid = 0, fused_team = 64;
   size_t fused_lds = 0;
@@ -672,6 +698,11 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       T.team = all32 ? 32 : 64;
     }
     T.lds = make_layout(M->info, M->n_levels, M->n_anc, T.team, elem_size);
+    // the dense step where its lanes and masks hold the model
+    T.dense = p->compute_fp64 && T.team == 64 && M->info.n_v >= 1 && M->info.n_v <= kDenseMaxV &&
+              M->info.n_links <= kDenseMaxLinks;
+    if (T.dense) T.dl = make_dense_layout(M->info, (int)M->tj_f.size(), (int)elem_size);
+    T.lds_bytes = (size_t)(T.dense ? T.dl.total : T.lds.total) * elem_size;
     // limit margins per joint type
     std::vector<double> lf = M->lf;
     for (int i = 0; i < M->info.n_links; ++i)
@@ -686,7 +717,8 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
         {lists[t].data(), lists[t].size() * 4}, {lf.data(), lf.size() * 8}, {M->sf.data(), M->sf.size() * 8},
         {M->link_anc.data(), M->link_anc.size() * 8}, {M->col_anc.data(), M->col_anc.size() * 8},
         {M->col_link.data(), M->col_link.size() * 4}, {M->tj_i.data(), M->tj_i.size() * 4},
-        {M->tj_f.data(), M->tj_f.size() * 8}, {M->tp.data(), M->tp.size() * 8}};
+        {M->tj_f.data(), M->tj_f.size() * 8}, {M->tp.data(), M->tp.size() * 8},
+        {M->link_cols.data(), M->link_cols.size() * 4}, {M->jump.data(), M->jump.size() * 4}};
     size_t total = 0;
     std::vector<size_t> offs;
     for (auto& q : parts) {
@@ -738,6 +770,9 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     D.tj_i = (const int*)(b + offs[16]);
     D.tj_f = (const double*)(b + offs[17]);
     D.tp = (const double*)(b + offs[18]);
+    D.link_cols = (const int*)(b + offs[19]);
+    D.jump = (const int*)(b + offs[20]);
+    D.n_jump = M->n_jump;
     T.body_pairs = M->body_pairs;
     const int adj_cap = p->adjoint_max_rows > 0 ? p->adjoint_max_rows : kAdjRows;
     const int adj_small_cap = std::min(adj_cap, kAdjSmallRows);
@@ -755,7 +790,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       return hip_fail(err, "sim: adjoint LDS limit");
     }
     // J and W rows (slow path), then the wide path's columns of A (one entry per lane of a 64-lane team)
-    T.scratch_stride = 2ll * D.r_cap * std::max(1, D.n_v) + (T.team == 64 ? 64ll * 64 : 0);
+    T.scratch_stride = 2ll * D.r_cap * std::max(1, D.n_v) + (T.team == 64 ? 64ll * 64 : 0) + (T.dense ? 4ll * D.r_cap : 0);
     T.scratch_stride = (T.scratch_stride + 63) & ~63ll;
     if (T.team == 64) {
       if ((err = hipMalloc(&T.step_order, 2 * sizeof(int) * T.n_envs)) != hipSuccess ||
@@ -774,13 +809,12 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       ags_sim_destroy(S);
       return hip_fail(err, "sim: scratch");
     }
-    const size_t lds_bytes = (size_t)T.lds.total * elem;
-    if (lds_bytes > 160 * 1024) {
+    if (T.lds_bytes > 160 * 1024) {
       S->types.push_back(T);
       ags_sim_destroy(S);
       return fail(AGS_E_ARG, "sim: model too large for one workgroup's LDS");
     }
-    if (lds_bytes > 64 * 1024 && (err = set_lds_limit(p->compute_fp64, T.team, lds_bytes)) != hipSuccess) {
+    if (!T.dense && T.lds_bytes > 64 * 1024 && (err = set_lds_limit(p->compute_fp64, T.team, T.lds_bytes)) != hipSuccess) {
       S->types.push_back(T);
       ags_sim_destroy(S);
       return hip_fail(err, "sim: LDS limit");
@@ -814,23 +848,25 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost(S->types[a]) > cost(S->types[b]); });
     std::vector<int> units;
-    size_t lds_words = 0;
+    S->fused_lds = 0;
+    S->fused_dense = true;
+    for (const TypeDev& T : S->types) S->fused_dense = S->fused_dense && T.dense;
     for (int k : order) {
       const TypeDev& T = S->types[k];
       const int epw = kTeam / T.team;
       const int groups = (T.n_envs + epw - 1) / epw;
       for (int g = 0; g < groups; ++g) units.insert(units.end(), {k, g});
-      lds_words = std::max(lds_words, (size_t)T.lds.total);
+      S->fused_lds = std::max(S->fused_lds, S->fused_dense ? T.lds_bytes : (size_t)T.lds.total * elem_size);
     }
     S->fused_team = S->types[0].team;
-    S->fused_lds = lds_words * elem_size;
     S->n_units = (int)(units.size() / 2);
     int dev = 0, cus = 0, per_cu = 0;
     if (S->fused_lds <= 160 * 1024 &&
         (err = hipGetDevice(&dev)) == hipSuccess &&
         (err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) == hipSuccess &&
         (S->fused_lds <= 64 * 1024 || (err = set_fused_lds_limit(p->compute_fp64, S->fused_team, S->fused_lds)) == hipSuccess) &&
-        (err = fused_blocks_per_cu(p->compute_fp64, S->fused_team, S->fused_lds, &per_cu)) == hipSuccess &&
+        (err = S->fused_dense ? dense_fused_blocks_per_cu(p->solver == AGS_SOLVER_TGS, S->fused_lds, &per_cu)
+                              : fused_blocks_per_cu(p->compute_fp64, S->fused_team, S->fused_lds, &per_cu)) == hipSuccess &&
         (err = hipMalloc(&S->units, units.size() * sizeof(int))) == hipSuccess &&
         (err = hipMemcpy(S->units, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice)) == hipSuccess) {
       S->fused_grid = std::max(1, std::min(S->n_units, cus * std::max(1, per_cu)));
@@ -959,6 +995,7 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
     TypeArgs t{};
     t.m = T.dm;
     t.lds = T.lds;
+    t.dl = T.dl;
     t.env_list = T.env_list;
     t.n_envs = T.n_envs;
     t.scratch = T.scratch;
@@ -971,7 +1008,9 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
     for (size_t k = 0; k < S->types.size(); ++k) f.types[k] = type_args(S->types[k]);
     f.units = S->units;
     f.n_units = S->n_units;
-    hipError_t e = launch_step_fused(f, S->fused_grid, S->fused_lds, p.compute_fp64, S->fused_team, (hipStream_t)stream);
+    hipError_t e = S->fused_dense
+                       ? launch_dense_fused(f, S->fused_grid, S->fused_lds, (hipStream_t)stream)
+                       : launch_step_fused(f, S->fused_grid, S->fused_lds, p.compute_fp64, S->fused_team, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "step: launch");
     return AGS_OK;
   }
@@ -983,7 +1022,8 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
   for (TypeDev& T : S->types) {
     a.ty = type_args(T);
     if (T.step_order) a.ty.env_list = T.step_order;
-    hipError_t e = launch_step(a, T.n_envs, p.compute_fp64, T.team, (hipStream_t)stream);
+    hipError_t e = T.dense ? launch_dense(a, T.n_envs, (hipStream_t)stream)
+                           : launch_step(a, T.n_envs, p.compute_fp64, T.team, (hipStream_t)stream);
     if (e == hipSuccess && T.step_order)
       e = launch_order_by_rows(T.step_order, T.order_tmp, S->env_rows, T.n_envs, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "step: launch");

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "ags_adj_layout.h"
+#include "ags_dense_layout.h"
 
 namespace ags {
 
@@ -67,6 +68,11 @@ struct DevModel {
   const unsigned long long* link_anc;  // per link: bit j set iff link j is an ancestor of it or itself
   const unsigned long long* col_anc;   // per column: bit j set iff column j precedes it on its path to the root
   const int* col_link;                 // per column: the link that owns it
+  // models the dense step takes (at most kDenseMaxV columns, kDenseMaxLinks links): per link, the columns that
+  // move it (bit mask) and the links its pose is composed with, 6 bits per pointer-jumping round (63: none)
+  const int* link_cols;
+  const int* jump;
+  int n_jump;
   // fixed tendons: n_tj tendon joints (4 ints each: tendon, DOF, column, parent joint or -1; coefficient),
   // 6 doubles per tendon (stiffness, damping, rest length, lower, upper, limit stiffness)
   int n_tj;
@@ -79,9 +85,11 @@ struct DevModel {
 struct TypeArgs {
   DevModel m;
   Lds lds;
+  DenseLds dl;
   const int* env_list;
   int n_envs;
-  void* scratch;           // per env: J rows then W rows, r_cap x n_v each, in the compute type
+  void* scratch;           // per env: J rows then W rows, r_cap x n_v each, in the compute type, then (64 lanes per
+                           // env) 64 x 64 entries of the Delassus matrix and (dense step) four row tables of r_cap
   long long scratch_stride;
 };
 
@@ -197,6 +205,10 @@ hipError_t launch_fill_int(int* p, int n, int value, hipStream_t stream);
 hipError_t launch_scale_by_kp(float* x, const float* kp, int n, hipStream_t stream);
 
 hipError_t launch_step(const StepArgs& a, int n_envs, int fp64, int team, hipStream_t stream);
+// the dense form of the FP64 step with one environment per wavefront (TypeArgs::dl), and its persistent launch
+hipError_t launch_dense(const StepArgs& a, int n_envs, hipStream_t stream);
+hipError_t launch_dense_fused(const FusedArgs& a, int grid, size_t lds_bytes, hipStream_t stream);
+hipError_t dense_fused_blocks_per_cu(int tgs, size_t lds_bytes, int* blocks);
 // reorders the env ids order[0, n) by rows[env], most first (tmp: n ints)
 hipError_t launch_order_by_rows(int* order, int* tmp, const int* rows, int n, hipStream_t stream);
 hipError_t set_lds_limit(int fp64, int team, size_t bytes);
