@@ -485,7 +485,8 @@ struct TypeDev {
   DevModel dm{};
   Lds lds{};
   bool dense = false;          // runs the dense step
-  DenseLds dl{};
+  int nc = 0;                  // its size class
+  DenseDyn dl{};
   size_t lds_bytes = 0;        // of a workgroup of its step
   void* block = nullptr;       // device tables
   int* env_list = nullptr;     // device env ids of this type
@@ -605,6 +606,7 @@ struct ags_sim {
   hipEvent_t ev_big_start = nullptr, ev_big_done = nullptr, ev_big_listed = nullptr;
   // persistent (fused) launch
   bool fused_ok = false, fused_dense = false;
+  int fused_nc = 0;
   int* units = nullptr;  // device: (type, group) pairs
   int n_units = 0, fused_grid = 0, fused_team = 64;
   size_t fused_lds = 0;
@@ -701,7 +703,11 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     // the dense step where its lanes and masks hold the model
     T.dense = p->compute_fp64 && T.team == 64 && M->info.n_v >= 1 && M->info.n_v <= kDenseMaxV &&
               M->info.n_links <= kDenseMaxLinks;
-    if (T.dense) T.dl = make_dense_layout(M->info, (int)M->tj_f.size(), (int)elem_size);
+    if (T.dense) {
+      T.nc = dense_class(M->info.n_v, M->info.n_links);
+      T.dense = 2 * (int)M->tj_f.size() <= dense_x_words(T.nc);  // lengths and rates of the tendon joints
+      T.dl = make_dense_layout(M->info, dense_fixed_words(T.nc));
+    }
     T.lds_bytes = (size_t)(T.dense ? T.dl.total : T.lds.total) * elem_size;
     // limit margins per joint type
     std::vector<double> lf = M->lf;
@@ -850,7 +856,15 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     std::vector<int> units;
     S->fused_lds = 0;
     S->fused_dense = true;
-    for (const TypeDev& T : S->types) S->fused_dense = S->fused_dense && T.dense;
+    for (const TypeDev& T : S->types) {
+      S->fused_dense = S->fused_dense && T.dense;
+      S->fused_nc = std::max(S->fused_nc, T.nc);
+    }
+    if (S->fused_dense)  // every type in the largest one's size class
+      for (TypeDev& T : S->types) {
+        T.dl = make_dense_layout(models[T.model]->info, dense_fixed_words(S->fused_nc));
+        T.lds_bytes = (size_t)T.dl.total * elem_size;
+      }
     for (int k : order) {
       const TypeDev& T = S->types[k];
       const int epw = kTeam / T.team;
@@ -865,7 +879,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
         (err = hipGetDevice(&dev)) == hipSuccess &&
         (err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) == hipSuccess &&
         (S->fused_lds <= 64 * 1024 || (err = set_fused_lds_limit(p->compute_fp64, S->fused_team, S->fused_lds)) == hipSuccess) &&
-        (err = S->fused_dense ? dense_fused_blocks_per_cu(p->solver == AGS_SOLVER_TGS, S->fused_lds, &per_cu)
+        (err = S->fused_dense ? dense_fused_blocks_per_cu(S->fused_nc, p->solver == AGS_SOLVER_TGS, S->fused_lds, &per_cu)
                               : fused_blocks_per_cu(p->compute_fp64, S->fused_team, S->fused_lds, &per_cu)) == hipSuccess &&
         (err = hipMalloc(&S->units, units.size() * sizeof(int))) == hipSuccess &&
         (err = hipMemcpy(S->units, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice)) == hipSuccess) {
@@ -1009,7 +1023,7 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
     f.units = S->units;
     f.n_units = S->n_units;
     hipError_t e = S->fused_dense
-                       ? launch_dense_fused(f, S->fused_grid, S->fused_lds, (hipStream_t)stream)
+                       ? launch_dense_fused(f, S->fused_nc, S->fused_grid, S->fused_lds, (hipStream_t)stream)
                        : launch_step_fused(f, S->fused_grid, S->fused_lds, p.compute_fp64, S->fused_team, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "step: launch");
     return AGS_OK;
@@ -1022,7 +1036,7 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
   for (TypeDev& T : S->types) {
     a.ty = type_args(T);
     if (T.step_order) a.ty.env_list = T.step_order;
-    hipError_t e = T.dense ? launch_dense(a, T.n_envs, (hipStream_t)stream)
+    hipError_t e = T.dense ? launch_dense(a, T.nc, T.n_envs, T.lds_bytes, (hipStream_t)stream)
                            : launch_step(a, T.n_envs, p.compute_fp64, T.team, (hipStream_t)stream);
     if (e == hipSuccess && T.step_order)
       e = launch_order_by_rows(T.step_order, T.order_tmp, S->env_rows, T.n_envs, (hipStream_t)stream);

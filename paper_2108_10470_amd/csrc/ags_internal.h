@@ -85,7 +85,7 @@ struct DevModel {
 struct TypeArgs {
   DevModel m;
   Lds lds;
-  DenseLds dl;
+  DenseDyn dl;
   const int* env_list;
   int n_envs;
   void* scratch;           // per env: J rows then W rows, r_cap x n_v each, in the compute type, then (64 lanes per
@@ -206,9 +206,10 @@ hipError_t launch_scale_by_kp(float* x, const float* kp, int n, hipStream_t stre
 
 hipError_t launch_step(const StepArgs& a, int n_envs, int fp64, int team, hipStream_t stream);
 // the dense form of the FP64 step with one environment per wavefront (TypeArgs::dl), and its persistent launch
-hipError_t launch_dense(const StepArgs& a, int n_envs, hipStream_t stream);
-hipError_t launch_dense_fused(const FusedArgs& a, int grid, size_t lds_bytes, hipStream_t stream);
-hipError_t dense_fused_blocks_per_cu(int tgs, size_t lds_bytes, int* blocks);
+// (nc: the size class, at least dense_class of every model)
+hipError_t launch_dense(const StepArgs& a, int nc, int n_envs, size_t lds_bytes, hipStream_t stream);
+hipError_t launch_dense_fused(const FusedArgs& a, int nc, int grid, size_t lds_bytes, hipStream_t stream);
+hipError_t dense_fused_blocks_per_cu(int nc, int tgs, size_t lds_bytes, int* blocks);
 // reorders the env ids order[0, n) by rows[env], most first (tmp: n ints)
 hipError_t launch_order_by_rows(int* order, int* tmp, const int* rows, int n, hipStream_t stream);
 hipError_t set_lds_limit(int fp64, int team, size_t bytes);
