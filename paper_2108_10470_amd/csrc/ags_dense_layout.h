@@ -22,48 +22,42 @@ constexpr int dense_class(int n_v, int n_links) {
   return n_v <= 15 && n_links <= 16 ? 16 : n_v <= 27 && n_links <= 28 ? 28 : 32;
 }
 
-// offsets in 8-byte words, except the integer arrays (t_*, rkr, rm), which are in ints
+constexpr int kDenseContacts = 21;  // contacts of an environment whose rows fit its lanes
+
+// Offsets in 8-byte words, except the integer arrays (t_*, lrow, rm, clk), which are in ints.  The overlays keep a
+// workgroup at 10-15 KB, so that the registers and not the LDS bound how many fit a CU.
 template <int NC>
 struct DenseLds {
   static constexpr int max2(int a, int b) { return a > b ? a : b; }
   // model masks: ancestors of a link, columns moving a link, columns of a row of M
   static constexpr int t_la = 0, t_lcm = NC, t_ccm = 2 * NC;
-  // live through a substep
-  static constexpr int qj = 3 * NC / 2, qd = qj + NC, vs = qd + NC, lam = vs + NC, u = lam + kDenseRows, rkr = 2 * (u + 64),
-                       org = u + 64 + kDenseRows / 2;
-  // dynamics region: column axes, link poses, link velocities (later the columns' momenta, then the rows' forces of
-  // one chunk in pose and V), per-link sums (later the mass matrix, then the rows' column masks); the Delassus matrix
-  // of at most kDenseLdsRows rows overlays the region from its start
-  static constexpr int S = org + 4, pose = S + 6 * NC, V = pose + kDensePose * NC, X = V + 6 * NC,
-                       x_words = max2(kDenseXStride * NC, NC * (NC + 1) / 2), rm = 2 * X, A = S;
-  // pairs of columns of the factor's inverse transpose, column pair m as (2 m + 2) x 2 words (before them, a 1 among
-  // 63 zeros)
-  static constexpr int G = max2(X + x_words, A + kDenseLdsRows * kDenseAStride), g_words = NC / 2 * (NC / 2 + 1) * 2;
-  static constexpr int fixed = G + g_words;  // then the model's root states and contact slots
-  static_assert(G % 2 == 0 && u % 2 == 0, "16-byte aligned pairs");
-  static_assert(kDensePose * NC + 6 * NC >= 6 * kDenseChunk && x_words >= kDenseRows, "overlaid arrays fit");
+  // live through a substep: positions, rates, v* (before it, the right-hand side), limit rows, reference point
+  static constexpr int qj = 3 * NC / 2, qd = qj + NC, vs = qd + NC, lrow = 2 * (vs + NC), org = vs + NC + 32;
+  // Dynamics region.  S: column axes.  pose: link poses.  V: link velocities, the columns' momenta, the factor's
+  // broadcast window, link velocities under v*.  X: per-link sums, the packed mass matrix and behind it a 1 among 63
+  // zeros; later the rows' column masks (rm), the coefficients of the factor's columns (co), the contacts (normal,
+  // point, distance, links) and the limit rows' biases.  The rows' forces of one chunk overlay pose and V.
+  static constexpr int S = org + 4, pose = S + 6 * NC, V = pose + kDensePose * NC, X = V + 6 * NC, strip = X + NC * (NC + 1) / 2,
+                       rm = 2 * X, co = X + 64, cn = X + 128, cx = cn + 66, cphi = cx + 66, clk = 2 * (cphi + 22),
+                       lbias = cphi + 34,
+                       x_words = max2(max2(kDenseXStride * NC, NC * (NC + 1) / 2 + 64), 128 + 66 + 66 + 34 + 64);
+  // The Delassus matrix of at most kDenseLdsRows rows overlays the region from its start, after the sweeps the impulses
+  // and the velocity change in the factor's columns.  G: pairs of columns of the factor's inverse transpose, column pair
+  // m as (2 m + 2) x 2 words, behind the Delassus matrix (over the tail of X, written when the mass matrix has been read).
+  static constexpr int A = S, lam = A, u = A + kDenseRows, G = A + kDenseLdsRows * kDenseAStride,
+                       g_words = NC / 2 * (NC / 2 + 1) * 2;
+  static constexpr int fixed = max2(X + x_words, G + g_words);  // then the model's root states
+  static_assert(S % 2 == 0 && V % 2 == 0 && co % 2 == 0 && u % 2 == 0 && G % 2 == 0, "16-byte aligned pairs");
+  static_assert(kDensePose * NC + 6 * NC >= 6 * kDenseChunk && 6 * NC >= 64, "overlaid arrays fit");
+  static_assert(lbias + 64 <= G, "the factor's columns leave what is read after them alone");
 };
 
-// the part that depends on the model, behind the class's fixed part
 struct DenseDyn {
   int root;   // 13 words per actor
-  int slots;  // normal (3 words), point (3) and distance of every slot, in three arrays
-  int sact, slk;  // ints per slot: first row or -1; links
   int total;  // words
 };
-
 inline DenseDyn make_dense_layout(const ags_model_info& info, int fixed_words) {
-  DenseDyn D{};
-  int off = fixed_words;
-  D.root = off;
-  off += (13 * info.n_actors + 1) & ~1;
-  D.slots = off;
-  off += 7 * info.n_slots;
-  D.sact = 2 * off;
-  D.slk = D.sact + info.n_slots;
-  off += info.n_slots;
-  D.total = (off + 1) & ~1;
-  return D;
+  return {fixed_words, (fixed_words + 13 * info.n_actors + 1) & ~1};
 }
 inline int dense_fixed_words(int nc) {
   return nc == 16 ? DenseLds<16>::fixed : nc == 28 ? DenseLds<28>::fixed : DenseLds<32>::fixed;

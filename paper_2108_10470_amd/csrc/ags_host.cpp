@@ -796,7 +796,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       return hip_fail(err, "sim: adjoint LDS limit");
     }
     // J and W rows (slow path), then the wide path's columns of A (one entry per lane of a 64-lane team)
-    T.scratch_stride = 2ll * D.r_cap * std::max(1, D.n_v) + (T.team == 64 ? 64ll * 64 : 0) + (T.dense ? 4ll * D.r_cap : 0);
+    T.scratch_stride = 2ll * D.r_cap * std::max(1, D.n_v) + (T.team == 64 ? 64ll * 64 : 0) + (T.dense ? 32ll * 64 + 3ll * D.r_cap + 8ll * D.n_slots : 0);
     T.scratch_stride = (T.scratch_stride + 63) & ~63ll;
     if (T.team == 64) {
       if ((err = hipMalloc(&T.step_order, 2 * sizeof(int) * T.n_envs)) != hipSuccess ||

@@ -89,7 +89,8 @@ struct TypeArgs {
   const int* env_list;
   int n_envs;
   void* scratch;           // per env: J rows then W rows, r_cap x n_v each, in the compute type, then (64 lanes per
-                           // env) 64 x 64 entries of the Delassus matrix and (dense step) four row tables of r_cap
+                           // env) 64 x 64 entries of the Delassus matrix and (dense step) tiles of Z^T, row tables
+                           // and contacts
   long long scratch_stride;
 };
 
