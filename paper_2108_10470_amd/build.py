@@ -12,7 +12,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libags.so")
-SOURCES = ["ags_dense.hip", "ags_step.hip", "ags_adjoint.hip", "ags_jacmass.hip", "ags_host.cpp"]
+SOURCES = ["ags_dense.hip", "ags_dense_adjoint.hip", "ags_step.hip", "ags_adjoint.hip", "ags_jacmass.hip", "ags_host.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # packed FP32 instructions are disabled for every HIP translation unit
@@ -21,16 +21,21 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
 
 
 def build(verbose: bool = False) -> str:
-    objs = []
-    for src in SOURCES:
+    objs, jobs = [], []
+    for src in SOURCES:  # compiled side by side
         path = os.path.join(CSRC, src)
         obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
         lang = ["-x", "hip"] if src.endswith(".cpp") else []
         cmd = [HIPCC, *FLAGS, *lang, "-c", path, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        jobs.append((cmd, subprocess.Popen(cmd)))
         objs.append(obj)
+    for cmd, job in jobs:
+        if job.wait() != 0:
+            for _, other in jobs:
+                other.wait()
+            raise subprocess.CalledProcessError(job.returncode, cmd)
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     if verbose:

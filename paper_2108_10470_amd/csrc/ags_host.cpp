@@ -501,6 +501,9 @@ struct TypeDev {
   size_t adj_bytes = 0;           // LDS of the adjoint kernel
   AdjLds adj_small{};             // the same with at most kAdjSmallRows rows (first pass of a two-pass adjoint)
   size_t adj_small_bytes = 0;
+  bool adj_dense = false;         // runs the dense adjoint, in the size class adj_nc
+  int adj_nc = 0;
+  DenseAdjDyn add{}, add_small{};  // its layouts for 64 and 32 rows
   bool adj_two = false;           // rows may exceed kAdjSmallRows: small layout first, overflow retried
   bool body_pairs = false;
 };
@@ -789,7 +792,30 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     T.adj_small_bytes = (size_t)T.adj_small.n_real * (adj_fp64(*p) ? sizeof(double) : sizeof(float)) +
                         (size_t)T.adj_small.n_int * sizeof(int);
     max_type_envs = std::max(max_type_envs, T.n_envs);
-    if (T.adj_bytes <= 160 * 1024 && T.adj_bytes > 64 * 1024 &&
+    // the dense adjoint where its lanes, masks and LDS hold the model
+    if (adj_fp64(*p) && M->info.n_v >= 1 && M->info.n_v <= kDenseMaxV && M->info.n_links <= kDenseMaxLinks) {
+      T.adj_nc = dense_class(M->info.n_v, M->info.n_links);
+      auto layout = [&](int cap, int big) {
+        return make_dense_adj_layout(M->info, p->substeps, std::min(p->pgs_iters, kAdjIters), cap,
+                                     dense_adj_fixed_words(T.adj_nc, big), big ? 64 : 32);
+      };
+      T.add = layout(adj_cap, T.adj_two);
+      T.add_small = layout(adj_small_cap, 0);
+      const size_t big = (size_t)T.add.total * sizeof(double), small = (size_t)T.add_small.total * sizeof(double);
+      // (512: the kernel's own LDS; a model whose general layout is refused stays refused)
+      T.adj_dense = big + 512 <= 160 * 1024 && T.adj_bytes <= 160 * 1024;
+      if (T.adj_dense) {
+        T.adj_bytes = big;
+        T.adj_small_bytes = small;
+        if ((big > 64 * 1024 && (err = set_dense_adjoint_lds_limit(T.adj_nc, T.adj_two, big)) != hipSuccess) ||
+            (small > 64 * 1024 && (err = set_dense_adjoint_lds_limit(T.adj_nc, 0, small)) != hipSuccess)) {
+          S->types.push_back(T);
+          ags_sim_destroy(S);
+          return hip_fail(err, "sim: adjoint LDS limit");
+        }
+      }
+    }
+    if (!T.adj_dense && T.adj_bytes <= 160 * 1024 && T.adj_bytes > 64 * 1024 &&
         (err = set_adjoint_lds_limit(adj_fp64(*p), T.adj_bytes)) != hipSuccess) {
       S->types.push_back(T);
       ags_sim_destroy(S);
@@ -1098,12 +1124,19 @@ extern "C" int ags_sim_step_backward(ags_sim* S, const float* root_state, const 
     a.mc = p.contact_margin;
     a.substeps = p.substeps;
     a.iters = p.pgs_iters;
+    a.dd = T.add;
+    // `big`: the form for all rows, otherwise the one for the first pass
+    auto launch = [&](const AdjArgs& x, bool big, hipStream_t on, int grid = 0) {
+      return T.adj_dense ? launch_dense_adjoint(x, T.adj_nc, big && T.adj_two, T.n_envs, on, grid)
+                         : launch_adjoint(x, T.n_envs, adj_fp64(p), on, grid);
+    };
     hipError_t e = hipSuccess;
     if (T.adj_two) {
       // pass 1 with the small layout (more workgroups per CU); environments with more rows are collected
       // and pass 2 runs them with the full layout
       AdjArgs a1 = a;
       a1.L = T.adj_small;
+      a1.dd = T.add_small;
       a1.retry_count = S->adj_retry;
       a1.retry = S->adj_retry + 1;
       AdjArgs a2 = a;
@@ -1136,17 +1169,17 @@ extern "C" int ags_sim_step_backward(ags_sim* S, const float* root_state, const 
             (e = launch_zero_count(S->adj_big_list, S->aux2)) == hipSuccess &&
             (e = launch_compact_flags(T.env_list, T.n_envs, S->adj_big, S->adj_big_list, S->aux2)) == hipSuccess &&
             (e = hipEventRecord(S->ev_big_listed, S->aux2)) == hipSuccess &&
-            (e = launch_adjoint(ab, T.n_envs, adj_fp64(p), S->aux2, S->n_cu * big_per_cu)) == hipSuccess)
+            (e = launch(ab, true, S->aux2, S->n_cu * big_per_cu)) == hipSuccess)
           e = hipEventRecord(S->ev_big_done, S->aux2);
         if (e == hipSuccess && gate) e = hipStreamWaitEvent(st, S->ev_big_listed, 0);
         if (e != hipSuccess) return hip_fail(e, "step_backward: flagged pass");
       }
       if ((e = launch_zero_count(S->adj_retry, st)) == hipSuccess &&
-          (e = launch_adjoint(a1, T.n_envs, adj_fp64(p), st)) == hipSuccess)
-        e = launch_adjoint(a2, T.n_envs, adj_fp64(p), st);
+          (e = launch(a1, false, st)) == hipSuccess)
+        e = launch(a2, true, st);
       if (e == hipSuccess && S->adj_big) e = hipStreamWaitEvent(st, S->ev_big_done, 0);
     } else {
-      e = launch_adjoint(a, T.n_envs, adj_fp64(p), (hipStream_t)stream);
+      e = launch(a, true, (hipStream_t)stream);
     }
     if (e != hipSuccess) return hip_fail(e, "step_backward: launch");
   }

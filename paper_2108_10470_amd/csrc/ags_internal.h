@@ -192,6 +192,7 @@ struct AdjArgs {
   const int* skip_flags;   // optional (indexed by env): envs whose flag is set are left to another launch
   double h, gx, gy, gz, mu, beta, mc;
   int substeps, iters;
+  DenseAdjDyn dd;          // layout of the dense form (L: of the general one)
 };
 
 // grid in (0, n_envs): that many workgroups stride over a device list (a.list_count required);
@@ -200,6 +201,9 @@ hipError_t launch_adjoint(const AdjArgs& a, int n_envs, int fp64, hipStream_t st
 // list[0] (zeroed beforehand) = count, list[1 ...] = the envs of env_list[0, n) with flags[env] != 0
 hipError_t launch_compact_flags(const int* env_list, int n, const int* flags, int* list, hipStream_t stream);
 hipError_t set_adjoint_lds_limit(int fp64, size_t bytes);
+// the dense form of the FP64 adjoint (size class nc; big: 64 rows, otherwise 32); grid as above
+hipError_t launch_dense_adjoint(const AdjArgs& a, int nc, int big, int n_envs, hipStream_t stream, int grid = 0);
+hipError_t set_dense_adjoint_lds_limit(int nc, int big, size_t bytes);
 hipError_t launch_zero_count(int* c, hipStream_t stream);
 hipError_t launch_fill_int(int* p, int n, int value, hipStream_t stream);
 
