@@ -31,7 +31,22 @@ struct Body {  // a link's mass, centre of mass and inertia about it, world axes
     const V3<R> p = mul(add(x.v, cross(x.w, c)), m);
     return SV{add(symv(x.w), cross(c, p)), p};
   }
+  // [m, m c, inertia about the reference point]
+  __device__ __forceinline__ void spatial(R* w) const {
+    const R cc = dot(c, c);
+    w[0] = m; w[1] = m * c.x; w[2] = m * c.y; w[3] = m * c.z;
+    w[4] = I[0] + m * (cc - c.x * c.x); w[5] = I[1] + m * (cc - c.y * c.y); w[6] = I[2] + m * (cc - c.z * c.z);
+    w[7] = I[3] - m * c.x * c.y; w[8] = I[4] - m * c.x * c.z; w[9] = I[5] - m * c.y * c.z;
+  }
 };
+// a composite inertia stored so (ten words at I), times x
+template <typename P>
+__device__ __forceinline__ SV comp_mul(const P& I, SV x) {
+  const V3<R> mc = mk(R(I[1]), R(I[2]), R(I[3]));
+  const V3<R> Jw = mk(I[4] * x.w.x + I[7] * x.w.y + I[8] * x.w.z, I[7] * x.w.x + I[5] * x.w.y + I[9] * x.w.z,
+                      I[8] * x.w.x + I[9] * x.w.y + I[6] * x.w.z);
+  return SV{add(Jw, cross(mc, x.v)), sub(mul(x.v, R(I[0])), cross(mc, x.w))};
+}
 __device__ __forceinline__ Body link_body(Gp<const double> lf, const R* Q, V3<R> o) {
   Body b;
   R Rw[9], T[9];
@@ -126,14 +141,13 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
   const int abase = gp(P->env_actor_base)[env], dbase = gp(P->env_dof_base)[env];
   const Lp<int> la = si_ + L::t_la, lcm = si_ + L::t_lcm, ccm = si_ + L::t_ccm;
   const Lp<R> dv = sm + L::dv, z_ = sm + L::z, qdda = sm + L::qdd, w_ = sm + L::w, vs = sm + L::vs, nu = sm + L::nu,
-              qj = sm + L::qj, nub = sm + L::nub, vsb = sm + L::vsb, nui = sm + L::nui, u = sm + L::u, nh = sm + L::nh,
-              uh = sm + L::uh, org = sm + L::org;
-  const Lp<R> S = sm + L::S, pose = sm + L::pose, V = sm + L::V, Acc = sm + L::Acc, Ic = sm + L::Ic, Fm = sm + L::Fm,
-              rowf = sm + L::rowf, lamy = sm + L::lamy, lbias = sm + L::lbias, cn = sm + L::cn, cx = sm + L::cx,
-              cphi = sm + L::cphi, X = sm + L::work, A_ = sm + L::work, Vs = sm + L::work;
+              qj = sm + L::qj, nub = sm + L::nub, vsb = nub, nui = sm + L::nui, u = sm + L::u, nh = sm + L::nh, org = sm + L::org;
+  const Lp<R> S = sm + L::S, pose = sm + L::pose, rowf = sm + L::rowf, lamy = sm + L::lamy, cn = sm + L::cn, cx = sm + L::cx,
+              cphi = sm + L::cphi, X = sm + L::X, V = sm + L::V, Acc = sm + L::Acc, Fm = sm + L::Fm, Vs = sm + L::Vs,
+              lbias = sm + L::lbias, A_ = sm + L::A, tape = sm + L::tape, sb = sm + L::sb;
   const Lp<d2> co = (Lp<d2>)(sm + L::co), G2 = (Lp<d2>)(sm + L::G);
   const Lp<int> rm = si_ + L::rm, lrow = si_ + L::lrow, clk = si_ + L::clk, cel = si_ + L::cel;
-  const Lp<R> tape = sm + P->dd.tape, st = sm + P->dd.st, rbar = sm + P->dd.rbar, nrb = sm + P->dd.nrb, dbar = sm + P->dd.dbar;
+  const Lp<R> st = sm + P->dd.st, rbar = sm + P->dd.rbar, dbar = sm + P->dd.dbar;
   const Lp<unsigned long long> mask = (Lp<unsigned long long>)(sm + P->dd.mask);
   const int iters4 = P->dd.iters4, sw = P->dd.state_words, subs = P->substeps;
 
@@ -184,14 +198,27 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
         for (int k = lane; k < 13 * na; k += 64) st[s * sw + k] = mr[k];
         for (int k = lane; k < 2 * nd; k += 64) st[s * sw + 13 * na + k] = md[k];
       }
-    // (vectors over columns are 32 words apart, dv first: entries past the model's columns stay zero)
+    // (entries of the vectors past the model's columns stay zero)
     for (int k = lane; k < L::org - L::dv; k += 64) dv[k] = R(0);
     for (int k = lane; k < L::g_words; k += 64) sm[L::G + k] = R(0);
-    for (int k = lane; k < 6 * 32; k += 64) S[k] = Fm[k] = R(0);
     wsync();
     if (lane < 3) org[lane] = st[lane];
     wsync();
   }
+  // velocities of the links and their velocity-product accelerations
+  auto velocities = [&]() {
+    const int cm0 = lcm[lc], cm1 = 16 + lc < NC ? lcm[min(16 + lc, NC - 1)] : 0;
+    path_sum<NC, true>(S, nu, V, cm0, cm1, lane);
+    if (lane < NC) {
+      // joint column: (V x s) qd; a free root's columns: its own term v x w on the linear part, once
+      SV c{zero3(), zero3()};
+      if (cl.joint()) c = mul6(crm(ld6(V + 6 * cl.link()), ld6(S + 6 * lane)), nu[lane]);
+      else if (cl.root0()) c.v = cross(ld3<R>(nu + lane), ld3<R>(nu + lane + 3));
+      st6(X + 6 * lane, c);
+    }
+    wsync();
+    path_sum<NC, false>(X, X, Acc, cm0, cm1, lane);
+  };
   R act_bar = R(0);  // column lane: adjoint of the joint's actuation
   bool ok = true;
   const R h = R(P->h), mu = R(P->mu);
@@ -231,28 +258,14 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       R Q[4];
       V3<R> o;
       poses<NC>(lfl, lk, P->m.n_jump, sin, qj, pose, S, org, nv, lane, Q, o);
-      const int cm0 = lcm[lc], cm1 = 16 + lc < NC ? lcm[min(16 + lc, NC - 1)] : 0;
-      path_sum<NC, true>(S, nu, V, cm0, cm1, lane);
-      if (lane < NC) {
-        // joint column: (V x s) qd; a free root's columns: its own term v x w on the linear part, once
-        SV c{zero3(), zero3()};
-        if (cl.joint()) c = mul6(crm(ld6(V + 6 * cl.link()), ld6(S + 6 * lane)), nu[lane]);
-        else if (cl.root0()) c.v = cross(ld3<R>(nu + lane), ld3<R>(nu + lane + 3));
-        st6(X + 6 * lane, c);
-      }
-      wsync();
-      path_sum<NC, false>(X, X, Acc, cm0, cm1, lane);
+      velocities();
       // every link's spatial inertia [m, m c, J] and the force it needs, about the reference point
       R w16[16];
 #pragma unroll
       for (int q = 0; q < 16; ++q) w16[q] = R(0);
       if (lk.is()) {
         const Body b = link_body(lfl, Q, o);
-        const V3<R> c = b.c;
-        const R m = b.m, cc = dot(c, c);
-        w16[0] = m; w16[1] = m * c.x; w16[2] = m * c.y; w16[3] = m * c.z;
-        w16[4] = b.I[0] + m * (cc - c.x * c.x); w16[5] = b.I[1] + m * (cc - c.y * c.y); w16[6] = b.I[2] + m * (cc - c.z * c.z);
-        w16[7] = b.I[3] - m * c.x * c.y; w16[8] = b.I[4] - m * c.x * c.z; w16[9] = b.I[5] - m * c.y * c.z;
+        b.spatial(w16);
         SV acc = ld6(Acc + 6 * lane);
         acc.v = sub(acc.v, mk(R(P->gx), R(P->gy), R(P->gz)));
         const SV vel = ld6(V + 6 * lane);
@@ -269,15 +282,10 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     // ---------------------------------------------------- subtree sums, mass matrix, factor
     subtree_sum<NC>(X, la, lane, X, la, 0);
     if (lane < NC) {
-#pragma unroll
-      for (int q = 0; q < 10; ++q) Ic[L::Ic_stride * lane + q] = X[kDenseXStride * lane + q];
       const Lp<R> Y = X + kDenseXStride * cl.link();
       const SV s = ld6(S + 6 * lane);  // zero past the model's columns
-      const V3<R> mc = mk(R(Y[1]), R(Y[2]), R(Y[3]));
-      const V3<R> Js = mk(Y[4] * s.w.x + Y[7] * s.w.y + Y[8] * s.w.z, Y[7] * s.w.x + Y[5] * s.w.y + Y[9] * s.w.z,
-                          Y[8] * s.w.x + Y[9] * s.w.y + Y[6] * s.w.z);
       vs[lane] = tau - dot6(s, SV{mk(R(Y[10]), R(Y[11]), R(Y[12])), mk(R(Y[13]), R(Y[14]), R(Y[15]))});
-      st6(Fm + 6 * lane, SV{add(Js, cross(mc, s.v)), sub(mul(s.v, R(Y[0])), cross(mc, s.w))});
+      st6(Fm + 6 * lane, comp_mul(Y, s));
     }
     wsync();
     {
@@ -355,7 +363,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       const R t = f.p1 * (s1 * s1), s2 = rsqrt_newton(fma_(-f.p1, t, f.p2));
       ca = lane >= nv ? R(0) : odd ? -t * s2 : s1;
       cb = lane >= nv || !odd ? R(0) : s2;
-      if (lane < 32) co[lane] = d2{ca, cb};
+      if (lane < NC) co[lane] = d2{ca, cb};
       wsync();
     }
     // (the right-hand side in vs past the columns is zero: their axes are)
@@ -615,6 +623,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     }
     R z = -(y + bias) * ia, rlam = R(0);
     if (lane < RC)
+#pragma unroll 4
       for (int r = 0; r < Rn; ++r) {
         const int q = r * AS + lane;
         A_[q] = r == lane ? R(0) : -ia * A_[q];
@@ -667,15 +676,12 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     if (!own) rlam = R(0);
     ADJ_PHASE(0);
     // ---------------------------------------------------- velocities after the impulses
-    if (lane < RC) {
-      lamy[lane] = rlam;
-      if (own) A_[lane * AS + lane] = R(-1);  // (the reverse update of a row takes its own t to zero)
-    }
+    if (lane < RC) lamy[lane] = rlam;
     wsync();
     zt_times(lamy, u);
     {
       const R d = times_G();
-      if (lane < 32) dv[lane] = d;
+      if (lane < NC) dv[lane] = d;
     }
     wsync();
     if (!reverse) {
@@ -719,14 +725,10 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     }
     for (int a = lane; a < na; a += 64) {
       const auto ai = gp(P->m.ai) + a * AI_COLS;
-      for (int k = 0; k < 13; ++k) nrb[13 * a + k] = R(0);
       if (ai[AI_FIXED]) continue;
       const int c = ai[AI_COL];
       const Lp<R> rb = rbar + 13 * a;
-      for (int k = 0; k < 3; ++k) {
-        nrb[13 * a + k] = rb[k];
-        nub[c + k] = rb[7 + k] + h * rb[k];
-      }
+      for (int k = 0; k < 3; ++k) nub[c + k] = rb[7 + k] + h * rb[k];
       const V3<R> th = mul(add(ld3<R>(vs + c + 3), ld3<R>(dv + c + 3)), h);
       R dq[4], q1[4];
       dq_of(th, dq);
@@ -745,7 +747,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       R q0b[4], dqb[4];
       qmul(dqc, qb1, q0b);
       qmul(qb1, q0c, dqb);
-      for (int k = 0; k < 4; ++k) nrb[13 * a + 3 + k] = q0b[k];
+      for (int k = 0; k < 4; ++k) rb[3 + k] = q0b[k];  // (the position's adjoint passes through)
       const V3<R> thb = dq_adj(th, dqb);
       nub[c + 3] = rb[10] + h * thb.x;
       nub[c + 4] = rb[11] + h * thb.y;
@@ -764,10 +766,11 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
         t2 = fma_(R(e.y), b, t2);
       }
       const R x = fma_(cb, t2, ca * t1);  // zero past the columns
-      if (lane < 32) nh[lane] = u[lane] = lane < nv ? x : R(0);
+      if (lane < NC) nh[lane] = lane < nv ? x : R(0);
+      if (lane < 32) u[lane] = lane < nv ? x : R(0);
       wsync();
       const R zc = times_G();
-      if (lane < 32) z_[lane] = zc;
+      if (lane < NC) z_[lane] = zc;
       wsync();
     }
     R t = R(0);
@@ -786,33 +789,65 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     // ---------------------------------------------------- Gauss-Seidel reverse
     R ybar = R(0);
     {
+      // The chain from row to row is a lane read and a multiply-add.  A row's own t, zero after its update, is not
+      // read again in the sweep: lanes subtract what they had at their own update (gc) after it.
       const Lp<R> arow = A_ + kk * AS;
       for (int it = iters - 1; it >= 0; --it) {
-        const unsigned long long fr = mask[2 * it], up = mask[2 * it + 1];
-        const int fr0 = __builtin_amdgcn_readfirstlane((int)fr), fr1 = __builtin_amdgcn_readfirstlane((int)(fr >> 32));
-        const int up0 = __builtin_amdgcn_readfirstlane((int)up), up1 = __builtin_amdgcn_readfirstlane((int)(up >> 32));
+        const unsigned long long fr_ = mask[2 * it], up_ = mask[2 * it + 1];
+        auto scalar = [](unsigned long long x) {
+          return (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)x) |
+                 (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32;
+        };
+        unsigned long long fr = scalar(fr_), up = scalar(up_);
+        const bool free_own = (fr >> lane) & 1;
         R gc = R(0);  // the lane's t when its own row was reversed
-        int k3 = 2;   // row r is a contact's normal, first or second tangent
-        R a_next = arow[max(Rn - 1, 0)];
-        for (int r = Rn - 1; r >= 0; --r) {
-          const R a = a_next;
-          a_next = arow[max(r - 1, 0)];
-          asm volatile("" ::: "memory");
-          const bool free = ((r < 32 ? fr0 : fr1) >> (r & 31)) & 1;
-          const R g = lane_read(t, r);
-          if (free) {
+        if (n_contacts > 0) {
+          fr <<= 64 - Rn;  // row r at the top bit
+          up <<= 64 - Rn;
+          const Lp<R> last = arow + Rn - 3;
+          R a0 = last[0], a1 = last[1], a2 = last[2];
+          for (int r = Rn - 3; r >= nlim; r -= 3) {
+            const R c0 = a0, c1 = a1, c2 = a2;
+            const Lp<R> next = arow + max(r - 3, 0);
+            a0 = next[0];
+            a1 = next[1];
+            a2 = next[2];
+            asm volatile("" ::: "memory");
+            auto friction = [&](int k, R c) {
+              const R g = lane_read(t, r + k);
+              gc = lane == r + k ? t : gc;
+              if ((long long)fr < 0) {
+                t = fma_(c, g, t);
+              } else {
+                const R m = (long long)up < 0 ? mu : -mu;
+                t = lane == r ? fma_(m, g, t) : t;
+              }
+              fr <<= 1;
+              up <<= 1;
+            };
+            friction(2, c2);
+            friction(1, c1);
+            const R g = lane_read(t, r);
             gc = lane == r ? t : gc;
-            t = fma_(a, g, t);
-          } else {
-            t = lane == r ? R(0) : t;
-            if (r >= nlim && k3 > 0) {
-              const bool hi = ((r < 32 ? up0 : up1) >> (r & 31)) & 1;
-              t = lane == r - k3 ? fma_(hi ? mu : -mu, g, t) : t;
-            }
+            if ((long long)fr < 0) t = fma_(c0, g, t);
+            fr <<= 1;
+            up <<= 1;
           }
-          k3 = k3 == 0 ? 2 : k3 - 1;
+        } else {
+          fr <<= 63 - max(Rn - 1, 0);
         }
-        ybar = own ? fma_(-ia, gc, ybar) : R(0);
+        R a0 = arow[max(nlim - 1, 0)];
+        for (int r = nlim - 1; r >= 0; --r) {
+          const R c0 = a0;
+          a0 = arow[max(r - 1, 0)];
+          asm volatile("" ::: "memory");
+          const R g = lane_read(t, r);
+          gc = lane == r ? t : gc;
+          if ((long long)fr < 0) t = fma_(c0, g, t);
+          fr <<= 1;
+        }
+        t -= gc;
+        ybar = own && free_own ? fma_(-ia, gc, ybar) : ybar;
         if (lane < RC) tape[(iters4 + it) * RC + lane] = ybar;
       }
     }
@@ -824,11 +859,11 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     ADJ_PHASE(3);
     // ---------------------------------------------------- v*bar = nubar + J^T ybar, w = h G (G^T nubar + Z^T ybar)
     zt_times(lamy + RC, u);
-    if (lane < 32) u[lane] = h * (nh[lane] + (lane < nv ? R(u[lane]) : R(0)));
+    if (lane < 32) u[lane] = lane < nv ? h * (nh[lane] + u[lane]) : R(0);
     wsync();
     {
       const R wc = times_G();
-      if (lane < 32) w_[lane] = wc;
+      if (lane < NC) w_[lane] = wc;
     }
     wsync();
     {
@@ -966,7 +1001,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
 #pragma unroll
         for (int b = 0; b <= a; ++b) {
           // dv z^T + z dv^T + qdd w^T + w qdd^T: one step
-          pm[a][b] = tile(dv[32 * lg + 16 * a + lc], dv[32 * (lg ^ 1) + 16 * b + lc], tile_zero());
+          pm[a][b] = tile(dv[NC * lg + 16 * a + lc], dv[NC * (lg ^ 1) + 16 * b + lc], tile_zero());
 #pragma unroll
           for (int n = a; n < CT; ++n)
 #pragma unroll
@@ -1014,7 +1049,6 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     }
     ADJ_PHASE(6);
     // ---------------------------------------------------- rows: axis adjoints of their columns, velocities under Jbar_r
-    const Lp<R> sb = tape;  // axis adjoint of every column (the tape is not read any more)
     const Lp<R> rv = X;     // per row 6 words
     {
       wsync();
@@ -1130,35 +1164,69 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       wsync();
     }
     ADJ_PHASE(4);
+    Body body;  // the lane's link
     // ---------------------------------------------------- d tr(M P)/dq, weight -1
     {
       const int lw = min(lc, 5);
+      auto keep = [](R x, int on) { return __hiloint2double(__double2hiint(x) & on, __double2loint(x) & on); };
       v4 y0 = tile_zero(), y1 = tile_zero(), e0 = tile_zero(), e1 = tile_zero();
-      const int m0 = ccm[lc] >> lg, m1 = (16 + lc < NC ? ccm[min(16 + lc, NC - 1)] : 0) >> lg;
+      R pe0[NC / 4], pe1[NC / 4];
+      {
+        const int m0 = ccm[lc] >> lg, m1 = (16 + lc < NC ? ccm[min(16 + lc, NC - 1)] : 0) >> lg;
 #pragma unroll
-      for (int k = 0; k < NC / 4; ++k) {
-        const int j = 4 * k + lg;
-        const R s = S[6 * j + lw], fm = Fm[6 * j + lw];
-        auto keep = [](R x, int on) { return __hiloint2double(__double2hiint(x) & on, __double2loint(x) & on); };
-        // sum over the columns j at or before k on its path: P_kj s_j
-        if (4 * k < 16) y0 = tile(keep(X[lc * ZS + j], __builtin_amdgcn_sbfe(m0, 4 * k, 1)), s, y0);
-        if (NC > 16) y1 = tile(keep(X[(16 + lc) * ZS + j], __builtin_amdgcn_sbfe(m1, 4 * k, 1)), s, y1);
-        // sum over the columns k below column j: P_kj F_k
-        const int mj = ccm[j];
-        e0 = tile(keep(X[j * ZS + lc], j > lc ? __builtin_amdgcn_sbfe(mj, lc, 1) : 0), fm, e0);
-        if (NC > 16 && 4 * k + 3 >= 16)
-          e1 = tile(keep(X[j * ZS + 16 + lc], j > 16 + lc ? __builtin_amdgcn_sbfe(mj, 16 + lc, 1) : 0), fm, e1);
+        for (int k = 0; k < NC / 4; ++k) {
+          const int j = 4 * k + lg;
+          const R s = S[6 * j + lw];
+          // sum over the columns j at or before k on its path: P_kj s_j
+          if (4 * k < 16) y0 = tile(keep(X[lc * ZS + j], __builtin_amdgcn_sbfe(m0, 4 * k, 1)), s, y0);
+          if (NC > 16) y1 = tile(keep(X[(16 + lc) * ZS + j], __builtin_amdgcn_sbfe(m1, 4 * k, 1)), s, y1);
+          // operands of the sum over the columns k below column j: P_kj F_k
+          const int mj = ccm[j];
+          pe0[k] = keep(X[j * ZS + lc], j > lc ? __builtin_amdgcn_sbfe(mj, lc, 1) : 0);
+          pe1[k] = NC > 16 && 4 * k + 3 >= 16 ? keep(X[j * ZS + 16 + lc], j > 16 + lc ? __builtin_amdgcn_sbfe(mj, 16 + lc, 1) : 0) : R(0);
+        }
       }
       const R pkk = lane < NC ? R(X[lane * ZS + lane]) : R(0);
       wsync();
+      // velocities, accelerations, composite inertias and momenta again
+      velocities();
+      R I10[10];
+      {
+#pragma unroll
+        for (int q = 0; q < 10; ++q) I10[q] = R(0);
+        if (lk.is()) {
+          const Lp<R> p = pose + kDensePose * lane;
+          const R Q[4] = {p[0], p[1], p[2], p[3]};
+          body = link_body(gp(P->m.lf) + lane * LF_COLS, Q, ld3<R>(p + 4));
+          body.spatial(I10);
+        }
+        wsync();
+        if (lane < NC) {
+#pragma unroll
+          for (int q = 0; q < 10; ++q) X[kDenseXStride * lane + q] = I10[q];
+        }
+        wsync();
+        subtree_sum<NC>(X, la, lane, X, la, 0);
+        const Lp<R> Y = X + kDenseXStride * cl.link();
+#pragma unroll
+        for (int q = 0; q < 10; ++q) I10[q] = Y[q];
+        if (lane < NC) st6(Fm + 6 * lane, comp_mul(I10, ld6(S + 6 * lane)));
+        wsync();
+#pragma unroll
+        for (int k = 0; k < NC / 4; ++k) {
+          const R fm = Fm[6 * (4 * k + lg) + lw];
+          e0 = tile(pe0[k], fm, e0);
+          if (NC > 16 && 4 * k + 3 >= 16) e1 = tile(pe1[k], fm, e1);
+        }
+      }
       if (lc < 6) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           X[6 * (4 * v + lg) + lc] = y0[v];
-          X[192 + 6 * (4 * v + lg) + lc] = e0[v];
+          X[6 * NC + 6 * (4 * v + lg) + lc] = e0[v];
           if (16 + 4 * v < NC) {
             X[6 * (16 + 4 * v + lg) + lc] = y1[v];
-            X[192 + 6 * (16 + 4 * v + lg) + lc] = e1[v];
+            X[6 * NC + 6 * (16 + 4 * v + lg) + lc] = e1[v];
           }
         }
       }
@@ -1167,12 +1235,8 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
 #pragma unroll
       for (int q = 0; q < 16; ++q) w16[q] = R(0);
       if (cl.is()) {
-        const SV s = ld6(S + 6 * lane), ya = ld6(X + 6 * lane), e = ld6(X + 192 + 6 * lane);
-        const Lp<R> I = Ic + L::Ic_stride * cl.link();
-        const V3<R> mc = mk(R(I[1]), R(I[2]), R(I[3]));
-        const V3<R> Jw = mk(I[4] * ya.w.x + I[7] * ya.w.y + I[8] * ya.w.z, I[7] * ya.w.x + I[5] * ya.w.y + I[9] * ya.w.z,
-                            I[8] * ya.w.x + I[9] * ya.w.y + I[6] * ya.w.z);
-        const SV Iy = SV{add(Jw, cross(mc, ya.v)), sub(mul(ya.v, R(I[0])), cross(mc, ya.w))};
+        const SV s = ld6(S + 6 * lane), ya = ld6(X + 6 * lane), e = ld6(X + 6 * NC + 6 * lane);
+        const SV Iy = comp_mul(I10, ya);
         st6(sb + 6 * lane, add6(ld6(sb + 6 * lane), mul6(add6(Iy, e), R(-2))));
         // y' = 2 y + P_kk s: -<s, I y'> per link below the column
         const SV yp = add6(mul6(ya, R(2)), mul6(s, -pkk));
@@ -1218,9 +1282,8 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       SV F{zero3(), zero3()}, Ab = F;
       V3<R> c_ = zero3();
       if (lk.is()) {
-        const Lp<R> k = X + kDenseXStride * lane, p = pose + kDensePose * lane;
-        const R Q[4] = {p[0], p[1], p[2], p[3]};
-        const Body b = link_body(gp(P->m.lf) + lane * LF_COLS, Q, ld3<R>(p + 4));
+        const Lp<R> k = X + kDenseXStride * lane;
+        const Body& b = body;
         const R q6[6] = {k[0], k[1], k[2], k[3], k[4], k[5]};
         const V3<R> c = b.c;
         c_ = c;
@@ -1340,10 +1403,10 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
         const R qh[4] = {q[0] / nq, q[1] / nq, q[2] / nq, q[3] / nq};
         R o4[4];
         qmul(t4, qh, o4);
-        rb[0] = nrb[13 * a] + Wc.v.x;
-        rb[1] = nrb[13 * a + 1] + Wc.v.y;
-        rb[2] = nrb[13 * a + 2] + Wc.v.z;
-        for (int k = 0; k < 4; ++k) rb[3 + k] = nrb[13 * a + 3 + k] + R(2) * o4[k] / nq;
+        rb[0] += Wc.v.x;
+        rb[1] += Wc.v.y;
+        rb[2] += Wc.v.z;
+        for (int k = 0; k < 4; ++k) rb[3 + k] += R(2) * o4[k] / nq;
         for (int k = 0; k < 6; ++k) rb[7 + k] = nui[lk.rootcol() + k];
       }
     }
@@ -1363,7 +1426,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
 }
 
 template <int NC, int RT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1))) void dense_adjoint_kernel(AdjArgs, int) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RT == 2 ? 2 : 1))) void dense_adjoint_kernel(AdjArgs, int) {
   struct Args {
     AdjArgs a;
     int n_envs;

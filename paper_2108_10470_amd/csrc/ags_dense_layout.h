@@ -66,68 +66,76 @@ inline int dense_x_words(int nc) {
   return nc == 16 ? DenseLds<16>::x_words : nc == 28 ? DenseLds<28>::x_words : DenseLds<32>::x_words;
 }
 
-// LDS of the dense adjoint (RT tiles of 16 rows), offsets in 8-byte words except t_*, rm, lrow, clk, cel (ints).
+// LDS of the dense adjoint (RT tiles of 16 rows), offsets in 8-byte words except t_*, rm, lrow, clk, cel (ints).  What the
+// reverse could recompute (velocities, accelerations, inertias, momenta) is not kept through the sweeps: five instead of
+// four workgroups of the humanoid's class would fit a CU with it, six fit without.
 template <int NC, int RT>
 struct DenseAdjLds {
   static constexpr int max2(int a, int b) { return a > b ? a : b; }
   static constexpr int rows = 16 * RT, contacts = rows / 3;
   static constexpr int A_stride = rows + 1, Z_stride = 33;  // odd: columns are read without bank conflicts
   static constexpr int t_la = 0, t_lcm = NC, t_ccm = 2 * NC;
-  // per column, 32 words each so that a lane group can step from one to the next: velocity change of the impulses,
-  // z = M^-1 nubar, free acceleration, w = M^-1 h v*bar; v*, rates, positions, nubar, v*bar, rate adjoints
-  static constexpr int dv = 3 * NC / 2, z = dv + 32, qdd = z + 32, w = qdd + 32, vs = w + 32, nu = vs + 32, qj = nu + 32,
-                       nub = qj + 32, vsb = nub + 32, nui = vsb + 32, u = nui + 32, nh = u + 64, uh = nh + 32, org = uh + 32;
-  // kept from the recomputation: column axes, link poses, velocities, accelerations, composite inertias, momenta, factor
-  static constexpr int Ic_stride = 11;
-  static constexpr int S = org + 4, pose = S + 6 * NC + (6 * (32 - NC)), V = pose + kDensePose * NC, Acc = V + 6 * NC,
-                       Ic = Acc + 6 * NC, Fm = Ic + Ic_stride * NC, G = Fm + 6 * 32, g_words = NC / 2 * (NC / 2 + 1) * 2,
+  // per column: velocity change of the impulses, z = M^-1 nubar, free acceleration, w = M^-1 h v*bar (these four one after
+  // the other: a lane group steps from one to the next); v*, rates, positions, nubar (then v*bar), rate adjoints, G^T nubar
+  static constexpr int dv = 3 * NC / 2, z = dv + NC, qdd = z + NC, w = qdd + NC, vs = w + NC, nu = vs + NC, qj = nu + NC,
+                       nub = qj + NC, nui = nub + NC, nh = nui + NC, u = nh + NC, org = u + 64;
+  // column axes, link poses, factor
+  static constexpr int S = org + 4, pose = S + 6 * NC, G = pose + kDensePose * NC, g_words = NC / 2 * (NC / 2 + 1) * 2,
                        co = G + g_words;
   // rows: forces (before them the factor's window, after them the contacts' wrenches), masks, impulses and their adjoints
-  static constexpr int rowf = co + 64, rm = 2 * (rowf + 6 * rows), lamy = rowf + 7 * rows, lbias = lamy + 2 * rows,
-                       lrow = 2 * (lbias + 64), cn = lbias + 64 + 32, cx = cn + 3 * contacts, cphi = cx + 3 * contacts,
-                       clk = 2 * (cphi + contacts), cel = clk + 2 * ((contacts + 1) / 2),
-                       work = (cel / 2 + contacts + 3) & ~1;
-  // work: per-link sums and records (17 words each, twice), the packed mass matrix, the Delassus matrix, rows x columns
-  // products, the column adjoint matrix
-  static constexpr int work_words = max2(max2(rows * A_stride, max2(rows, 32) * Z_stride), 34 * 32);
-  static constexpr int fixed = (work + work_words + 1) & ~1;
+  static constexpr int rowf = co + 2 * NC, rm = 2 * (rowf + 6 * rows), lamy = rowf + 7 * rows, cx = lamy + 2 * rows,
+                       cel = 2 * (cx + 3 * contacts), work = (cx + 4 * contacts + 3) & ~1;
+  // work, before the rows: X (17 words per link, then the packed mass matrix and a 1 among zeros), velocities,
+  // accelerations, momenta; then velocities under v*, limits and contacts; then the Delassus matrix and behind it the tape;
+  // then rows x columns products (X of the reverse), P; then again X, velocities, accelerations, momenta
+  static constexpr int X = work, V = X + max2(kDenseXStride * NC, NC * (NC + 1) / 2 + 64), Acc = V + 6 * NC, Fm = Acc + 6 * NC,
+                       Vs = work, lbias = Vs + 6 * NC, lrow = 2 * (lbias + 64), cn = lbias + 96, cphi = cn + 3 * contacts,
+                       clk = 2 * (cphi + contacts), A = work, tape = A + rows * A_stride,
+                       sb = max2(Fm + 6 * NC, work + max2(rows, 32) * Z_stride),  // axis adjoint of every column
+                       fixed = sb + 6 * NC;
   static_assert(S % 2 == 0 && G % 2 == 0 && co % 2 == 0 && rowf % 2 == 0 && u % 2 == 0 && work % 2 == 0, "16-byte aligned pairs");
-  static_assert(NC * (NC + 1) / 2 + 64 <= work_words && 6 * (2 * contacts + 4) <= 6 * rows, "overlaid arrays fit");
+  static_assert(6 * (2 * contacts + 4) <= 6 * rows && cphi + 2 * contacts <= fixed, "overlaid arrays fit");
 };
 
 struct DenseAdjDyn {
-  int tape;                    // per sweep and row: change of the impulse, then (reverse) the row adjoint after the sweep
-  int iters4;                  // sweeps, rounded up to the contraction step of a tile
-  int mask;                    // per sweep: bits of the rows updated freely, of those at the upper bound
-  int st, rbar, nrb, dbar;     // state at every substep's start; adjoints of roots, of their pose, of DOFs
+  int iters4;               // sweeps, rounded up to the contraction step of a tile.  Tape: per sweep and row the change of
+                            // the impulse, then (reverse) the row adjoint after the sweep
+  int mask;                 // per sweep: bits of the rows updated freely, of those at the upper bound
+  int st, rbar, dbar;       // state at every substep's start; adjoints of roots and of DOFs
   int state_words, rows_cap, total;
 };
-inline DenseAdjDyn make_dense_adj_layout(const ags_model_info& info, int substeps, int iters, int row_cap, int fixed_words,
+inline DenseAdjDyn make_dense_adj_layout(const ags_model_info& info, int substeps, int iters, int row_cap, int fixed, int tape,
                                          int rows) {
   DenseAdjDyn d{};
   d.iters4 = (iters + 3) & ~3;
-  int off = fixed_words;
+  d.mask = tape + 2 * d.iters4 * rows;
+  int off = d.mask + 2 * d.iters4;
+  off = ((off > fixed ? off : fixed) + 1) & ~1;
   auto take = [&](int n) {
     const int o = off;
-    off += (n + 1) & ~1;
+    off += n;
     return o;
   };
-  d.tape = take(2 * d.iters4 * rows > 192 ? 2 * d.iters4 * rows : 192);
-  d.mask = take(2 * d.iters4);
   d.state_words = 13 * info.n_actors + 2 * info.n_dof;
   d.st = take(substeps * d.state_words);
   d.rbar = take(13 * info.n_actors);
-  d.nrb = take(13 * info.n_actors);
   d.dbar = take(2 * info.n_dof);
   const int rc = info.max_rows > 1 ? info.max_rows : 1;
   d.rows_cap = rc < row_cap ? rc : row_cap;
   d.total = off;
   return d;
 }
-inline int dense_adj_fixed_words(int nc, int big) {
-  return nc == 16   ? (big ? DenseAdjLds<16, 4>::fixed : DenseAdjLds<16, 2>::fixed)
-         : nc == 28 ? (big ? DenseAdjLds<28, 4>::fixed : DenseAdjLds<28, 2>::fixed)
-                    : (big ? DenseAdjLds<32, 4>::fixed : DenseAdjLds<32, 2>::fixed);
+template <int NC, int RT>
+inline DenseAdjDyn make_dense_adj_layout(const ags_model_info& info, int substeps, int iters, int row_cap) {
+  using L = DenseAdjLds<NC, RT>;
+  return make_dense_adj_layout(info, substeps, iters, row_cap, L::fixed, L::tape, L::rows);
+}
+inline DenseAdjDyn make_dense_adj_layout(int nc, int big, const ags_model_info& info, int substeps, int iters, int row_cap) {
+  if (nc == 16)
+    return big ? make_dense_adj_layout<16, 4>(info, substeps, iters, row_cap) : make_dense_adj_layout<16, 2>(info, substeps, iters, row_cap);
+  if (nc == 28)
+    return big ? make_dense_adj_layout<28, 4>(info, substeps, iters, row_cap) : make_dense_adj_layout<28, 2>(info, substeps, iters, row_cap);
+  return big ? make_dense_adj_layout<32, 4>(info, substeps, iters, row_cap) : make_dense_adj_layout<32, 2>(info, substeps, iters, row_cap);
 }
 
 }  // namespace ags

@@ -796,8 +796,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     if (adj_fp64(*p) && M->info.n_v >= 1 && M->info.n_v <= kDenseMaxV && M->info.n_links <= kDenseMaxLinks) {
       T.adj_nc = dense_class(M->info.n_v, M->info.n_links);
       auto layout = [&](int cap, int big) {
-        return make_dense_adj_layout(M->info, p->substeps, std::min(p->pgs_iters, kAdjIters), cap,
-                                     dense_adj_fixed_words(T.adj_nc, big), big ? 64 : 32);
+        return make_dense_adj_layout(T.adj_nc, big, M->info, p->substeps, std::min(p->pgs_iters, kAdjIters), cap);
       };
       T.add = layout(adj_cap, T.adj_two);
       T.add_small = layout(adj_small_cap, 0);
