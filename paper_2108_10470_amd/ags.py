@@ -201,6 +201,7 @@ class Sim:
                  rigid_body_state: bool = False, status: bool = False, adjoint_max_rows: int = 0):
         self.models = list(models)
         self.env_model = [int(x) for x in env_model]
+        self._model_envs = [self.env_model.count(m) for m in range(len(self.models))]  # environments of each model
         self.params = params
         self.device = torch.device(device)
         self.n_envs = len(env_model)
@@ -305,7 +306,7 @@ class Sim:
         output not asked for."""
         if not 0 <= model < len(self.models):
             raise ValueError(f"jacobian_mass: model {model} is not one of this sim's {len(self.models)} models")
-        n = sum(1 for m in self.env_model if m == model)
+        n = self._model_envs[model]
         info = self.models[model].info
         f32 = dict(dtype=torch.float32, device=self.device)
         J = torch.empty((n, info.n_links, 6, info.n_v), **f32) if jacobian else None
