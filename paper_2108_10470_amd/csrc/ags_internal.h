@@ -215,7 +215,8 @@ hipError_t launch_step(const StepArgs& a, int n_envs, int fp64, int team, hipStr
 hipError_t launch_dense(const StepArgs& a, int nc, int n_envs, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_dense_fused(const FusedArgs& a, int nc, int grid, size_t lds_bytes, hipStream_t stream);
 hipError_t dense_fused_blocks_per_cu(int nc, int tgs, size_t lds_bytes, int* blocks);
-// reorders the env ids order[0, n) by rows[env], most first (tmp: n ints)
+// reorders the env ids order[0, n) by rows[env], most first (tmp: order_tmp_ints(n) ints)
+size_t order_tmp_ints(int n);
 hipError_t launch_order_by_rows(int* order, int* tmp, const int* rows, int n, hipStream_t stream);
 hipError_t set_lds_limit(int fp64, int team, size_t bytes);
 hipError_t launch_set_rows(float* dst, const float* src, const int* idx, int n, int n_actors, const int* table,

@@ -1807,65 +1807,123 @@ static const void* step_fn(int fp64, int team) {
 }
 
 // Counting sort of the env ids of one type by the rows of their last step, most rows first (rows of
-// kOrderBuckets - 1 or more share the first bucket).  One workgroup; each thread keeps the ids and buckets
-// of its kOrderPer entries in registers between the count and the scatter, and batches of up to
-// kOrderLds ids are placed in LDS before one coalesced write (larger batches go through tmp).  The order
-// within a bucket is whichever the LDS atomics give, which no result depends on.
+// kOrderBuckets - 1 or more share the first bucket).  The order within a bucket is whichever the LDS atomics give, which
+// no result depends on.  Up to kOrderBlock ids: one workgroup, ids and ranks in registers between the count and the
+// scatter.  More: a workgroup per kOrderBlock ids counts (and copies its ids to tmp), a second launch adds up the counts
+// and scatters; one workgroup for all took 136 us for 65536 ids, two launches take 14.  It is bound by latency (two
+// dependent loads, the ranks, the scan): the lanes of a wavefront with the same bucket are found by ballots and one of
+// them asks LDS for all (4096 ids have a dozen buckets: an atomic per lane is serialised per address), the buckets are
+// scanned by a wavefront.
 constexpr int kOrderBuckets = 128;
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderPer = 8;
-constexpr int kOrderLds = kOrderThreads * kOrderPer;
-__global__ __launch_bounds__(kOrderThreads) void order_by_rows_kernel(int* order, int* tmp, const int* rows, int n) {
-  __shared__ int start[kOrderBuckets];
-  __shared__ int placed[kOrderLds];
+constexpr int kOrderBlock = kOrderThreads * kOrderPer;
+__device__ __forceinline__ int order_bucket(const int* rows, int e) {
+  return kOrderBuckets - 1 - min(max(rows[e], 0), kOrderBuckets - 1);
+}
+// adds one to the lane's counter (where `on`); returns the counter's value before the lane's own addition
+__device__ __forceinline__ int order_rank(int* counters, int bucket, bool on) {
+  unsigned long long same = __ballot(on);
+#pragma unroll
+  for (int b = 1; b < kOrderBuckets; b <<= 1) {
+    const unsigned long long m = __ballot(bucket & b);
+    same &= bucket & b ? m : ~m;
+  }
+  const int lane = threadIdx.x & 63, first = on ? __ffsll((long long)same) - 1 : 0;
+  int base = 0;
+  if (on && lane == first) base = atomicAdd(&counters[bucket], __popcll(same));
+  return __shfl(base, first, 64) + __popcll(same & lanes_below(lane));
+}
+// replaces the counters by their exclusive prefix sums (threads 0 ... 63; the caller synchronises)
+__device__ __forceinline__ void order_scan(int* counters) {
+  static_assert(kOrderBuckets == 128, "two per lane");
   const int t = threadIdx.x;
-  const bool in_lds = n <= kOrderLds;
-  auto bucket = [&](int e) { return kOrderBuckets - 1 - min(max(rows[e], 0), kOrderBuckets - 1); };
+  const int a = counters[2 * t], b = counters[2 * t + 1];
+  int sum = a + b;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int x = __shfl_up(sum, d, 64);
+    if (t >= d) sum += x;
+  }
+  counters[2 * t] = sum - a - b;
+  counters[2 * t + 1] = sum - b;
+}
+__global__ __launch_bounds__(kOrderThreads) void order_by_rows_kernel(int* order, const int* rows, int n) {
+  __shared__ int start[kOrderBuckets];
+  const int t = threadIdx.x;
   if (t < kOrderBuckets) start[t] = 0;
-  __syncthreads();
-  int ids[kOrderPer], bk[kOrderPer];
+  int ids[kOrderPer], bk[kOrderPer], rank[kOrderPer];
 #pragma unroll
   for (int k = 0; k < kOrderPer; ++k) {
     const int i = t + k * kOrderThreads;
     ids[k] = i < n ? order[i] : 0;
-    bk[k] = i < n ? bucket(ids[k]) : 0;
   }
+#pragma unroll
+  for (int k = 0; k < kOrderPer; ++k) bk[k] = t + k * kOrderThreads < n ? order_bucket(rows, ids[k]) : 0;
+  __syncthreads();
 #pragma unroll
   for (int k = 0; k < kOrderPer; ++k)
-    if (t + k * kOrderThreads < n) atomicAdd(&start[bk[k]], 1);
-  for (int i = t + kOrderLds; i < n; i += kOrderThreads) atomicAdd(&start[bucket(order[i])], 1);
+    if (k * kOrderThreads < n) rank[k] = order_rank(start, bk[k], t + k * kOrderThreads < n);
   __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int b = 0; b < kOrderBuckets; ++b) {
-      const int c = start[b];
-      start[b] = run;
-      run += c;
-    }
-  }
+  if (t < 64) order_scan(start);
   __syncthreads();
 #pragma unroll
+  for (int k = 0; k < kOrderPer; ++k)
+    if (t + k * kOrderThreads < n) order[start[bk[k]] + rank[k]] = ids[k];
+}
+__global__ __launch_bounds__(kOrderThreads) void order_count_kernel(const int* order, int* tmp, int* counts, const int* rows, int n) {
+  __shared__ int count[kOrderBuckets];
+  const int t = threadIdx.x;
+  if (t < kOrderBuckets) count[t] = 0;
+  __syncthreads();
   for (int k = 0; k < kOrderPer; ++k) {
-    if (t + k * kOrderThreads < n) {
-      const int pos = atomicAdd(&start[bk[k]], 1);
-      if (in_lds) placed[pos] = ids[k];
-      else tmp[pos] = ids[k];
-    }
-  }
-  for (int i = t + kOrderLds; i < n; i += kOrderThreads) {
-    const int e = order[i];
-    tmp[atomicAdd(&start[bucket(e)], 1)] = e;
+    const int i = blockIdx.x * kOrderBlock + t + k * kOrderThreads;
+    const int e = i < n ? order[i] : 0;
+    if (i < n) tmp[i] = e;
+    order_rank(count, i < n ? order_bucket(rows, e) : 0, i < n);
   }
   __syncthreads();
-  if (in_lds)
-    for (int i = t; i < n; i += kOrderThreads) order[i] = placed[i];
-  else
-    for (int i = t; i < n; i += kOrderThreads) order[i] = tmp[i];
+  if (t < kOrderBuckets) counts[blockIdx.x * kOrderBuckets + t] = count[t];
+}
+__global__ __launch_bounds__(kOrderThreads) void order_place_kernel(int* order, const int* tmp, const int* counts, const int* rows, int n) {
+  __shared__ int start[kOrderBuckets];
+  const int t = threadIdx.x;
+  int before = 0;
+  if (t < kOrderBuckets) {
+    int all = 0;
+    for (int b = 0; b < (int)gridDim.x; ++b) {
+      const int c = counts[b * kOrderBuckets + t];
+      before += b < (int)blockIdx.x ? c : 0;
+      all += c;
+    }
+    start[t] = all;
+  }
+  __syncthreads();
+  if (t < 64) order_scan(start);
+  __syncthreads();
+  if (t < kOrderBuckets) start[t] += before;
+  __syncthreads();
+  for (int k = 0; k < kOrderPer; ++k) {
+    const int i = blockIdx.x * kOrderBlock + t + k * kOrderThreads;
+    const int e = i < n ? tmp[i] : 0;
+    const int pos = order_rank(start, i < n ? order_bucket(rows, e) : 0, i < n);
+    if (i < n) order[pos] = e;
+  }
+}
+
+size_t order_tmp_ints(int n) {
+  return n <= kOrderBlock ? 0 : (size_t)n + (size_t)((n + kOrderBlock - 1) / kOrderBlock) * kOrderBuckets;
 }
 
 hipError_t launch_order_by_rows(int* order, int* tmp, const int* rows, int n, hipStream_t stream) {
   if (n <= 1) return hipSuccess;
-  hipLaunchKernelGGL(order_by_rows_kernel, dim3(1), dim3(kOrderThreads), 0, stream, order, tmp, rows, n);
+  if (n <= kOrderBlock) {
+    hipLaunchKernelGGL(order_by_rows_kernel, dim3(1), dim3(kOrderThreads), 0, stream, order, rows, n);
+  } else {
+    const int blocks = (n + kOrderBlock - 1) / kOrderBlock;
+    hipLaunchKernelGGL(order_count_kernel, dim3(blocks), dim3(kOrderThreads), 0, stream, order, tmp, tmp + n, rows, n);
+    hipLaunchKernelGGL(order_place_kernel, dim3(blocks), dim3(kOrderThreads), 0, stream, order, tmp, tmp + n, rows, n);
+  }
   return hipGetLastError();
 }
 
