@@ -648,20 +648,27 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       }
       if (n_contacts > 0) {
         acol = A_ + nlim * AS + kk;
-        a0 = acol[0];
-        R a1 = acol[AS], a2 = acol[2 * AS];
-        for (int r = nlim; r < Rn; r += 3) {
-          const R c0 = a0, c1 = a1, c2 = a2;
-          acol += r + 3 < Rn ? 3 * AS : 0;
-          a0 = acol[0];
-          a1 = acol[AS];
-          a2 = acol[2 * AS];
+        auto contact = [&](const R* c, int r) {
+          const R n = clamp_low0(z), m = lane_read(mu * n, r);
+          apply(n, c[0], r);
+          apply(clamp_sym(z, m), c[1], r + 1);
+          apply(clamp_sym(z, m), c[2], r + 2);
+        };
+        auto load = [&](R* c, int r) {  // columns r ... (past the last contact: that contact's)
+          acol += r < Rn ? 3 * AS : 0;
+          c[0] = acol[0];
+          c[1] = acol[AS];
+          c[2] = acol[2 * AS];
           asm volatile("" ::: "memory");
-          const R n = clamp_low0(z);
-          const R m = mu * lane_read(n, r);
-          apply(n, c0, r);
-          apply(clamp_sym(z, m), c1, r + 1);
-          apply(clamp_sym(z, m), c2, r + 2);
+        };
+        R ca3[3] = {acol[0], acol[AS], acol[2 * AS]}, cb3[3];
+        for (int r = nlim;;) {
+          load(cb3, r + 3);
+          contact(ca3, r);
+          if ((r += 3) >= Rn) break;
+          load(ca3, r + 3);
+          contact(cb3, r);
+          if ((r += 3) >= Rn) break;
         }
       }
       if (reverse) {
