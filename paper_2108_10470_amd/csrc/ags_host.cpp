@@ -1208,7 +1208,9 @@ extern "C" int ags_sim_jacobian_mass(ags_sim* S, int32_t model, float* jac, floa
   a.mass = mass;
   a.env_body_base = S->env_tables + 2 * S->n_envs;
   a.mass_scale = (const float*)S->bound[AGS_BODY_MASS_SCALE];
-  const hipError_t e = launch_jacmass(a, (hipStream_t)stream);
+  const bool dense = a.m.n_v >= 1 && a.m.n_v <= kDenseMaxV && a.m.n_links <= kDenseMaxLinks;
+  const hipError_t e = dense ? launch_dense_jacmass(a, dense_class(a.m.n_v, a.m.n_links), (hipStream_t)stream)
+                             : launch_jacmass(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "jacobian_mass: launch");
   return AGS_OK;
 }

@@ -164,6 +164,7 @@ struct JacMassArgs {
 };
 size_t jacmass_lds_bytes(int n_links, int n_v);
 hipError_t launch_jacmass(const JacMassArgs& a, hipStream_t stream);
+hipError_t launch_dense_jacmass(const JacMassArgs& a, int nc, hipStream_t stream);  // the dense form, size class nc
 
 // ---------------------------------------------------------------- adjoint of one env-step
 struct AdjArgs {
