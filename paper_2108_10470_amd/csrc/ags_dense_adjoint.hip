@@ -325,6 +325,8 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       n_contacts += __popcll(m);
     }
     wsync();
+    nlim = __builtin_amdgcn_readfirstlane(nlim);  // (the same in every lane, which the compiler does not see)
+    n_contacts = __builtin_amdgcn_readfirstlane(n_contacts);
     const int Rn = nlim + 3 * n_contacts;
     if (Rn > P->dd.rows_cap) {
       ok = false;
@@ -498,40 +500,42 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
     for (int it = 0; it < iters; ++it) {
       const R lam0 = rlam;
       R zc = R(0);  // the lane's z when its own row was updated
-      auto apply = [&](R cand, R a, int r) {
-        zc = lane == r ? z : zc;
-        row_apply(z, rlam, cand, a, r, lane);
+      unsigned long long bit = 1;
+      auto apply = [&](R cand, R a, int r, unsigned long long at) {
+        zc = pick(zc, z, at);
+        row_apply(z, rlam, cand, a, r, at);
       };
+      // (columns past the last row are read within the workgroup's LDS and not used)
       Lp<R> acol = A_ + kk;
       R a0 = acol[0];
-      for (int r = 0; r < nlim; ++r) {
+      for (int r = 0; r < nlim; ++r, bit <<= 1) {
         const R a = a0;
-        acol += r + 1 < Rn ? AS : 0;
+        acol += AS;
         a0 = acol[0];
         asm volatile("" ::: "memory");
-        apply(clamp_low0(z), a, r);
+        apply(clamp_low0(z), a, r, bit);
       }
       if (n_contacts > 0) {
-        acol = A_ + nlim * AS + kk;
         auto contact = [&](const R* c, int r) {
           const R n = clamp_low0(z), m = lane_read(mu * n, r);
-          apply(n, c[0], r);
-          apply(clamp_sym(z, m), c[1], r + 1);
-          apply(clamp_sym(z, m), c[2], r + 2);
+          apply(n, c[0], r, bit);
+          apply(clamp_sym(z, m), c[1], r + 1, bit << 1);
+          apply(clamp_sym(z, m), c[2], r + 2, bit << 2);
+          bit <<= 3;
         };
-        auto load = [&](R* c, int r) {  // columns r ... (past the last contact: that contact's)
-          acol += r < Rn ? 3 * AS : 0;
+        auto load = [&](R* c) {
+          acol += 3 * AS;
           c[0] = acol[0];
           c[1] = acol[AS];
           c[2] = acol[2 * AS];
           asm volatile("" ::: "memory");
         };
-        R ca3[3] = {acol[0], acol[AS], acol[2 * AS]}, cb3[3];
+        R ca3[3] = {a0, acol[AS], acol[2 * AS]}, cb3[3];
         for (int r = nlim;;) {
-          load(cb3, r + 3);
+          load(cb3);
           contact(ca3, r);
           if ((r += 3) >= Rn) break;
-          load(ca3, r + 3);
+          load(ca3);
           contact(cb3, r);
           if ((r += 3) >= Rn) break;
         }
@@ -676,47 +680,57 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
         if (n_contacts > 0) {
           fr <<= 64 - Rn;  // row r at the top bit
           up <<= 64 - Rn;
+          // (entries before the first row are read within the workgroup's LDS and not used)
           const Lp<R> last = arow + Rn - 3;
-          R a0 = last[0], a1 = last[1], a2 = last[2];
-          for (int r = Rn - 3; r >= nlim; r -= 3) {
-            const R c0 = a0, c1 = a1, c2 = a2;
-            const Lp<R> next = arow + max(r - 3, 0);
-            a0 = next[0];
-            a1 = next[1];
-            a2 = next[2];
+          unsigned long long bit = 1ull << (Rn - 3);
+          Lp<R> at = last;
+          R ca3[3] = {at[0], at[1], at[2]}, cb3[3];
+          auto load = [&](R* c) {
+            at -= 3;
+            c[0] = at[0];
+            c[1] = at[1];
+            c[2] = at[2];
             asm volatile("" ::: "memory");
-            auto friction = [&](int k, R c) {
+          };
+          auto contact = [&](const R* c, int r) {
+#pragma unroll
+            for (int k = 2; k >= 0; --k) {
               const R g = lane_read(t, r + k);
-              gc = lane == r + k ? t : gc;
-              if ((long long)fr < 0) {
-                t = fma_(c, g, t);
-              } else {
-                const R m = (long long)up < 0 ? mu : -mu;
-                t = lane == r ? fma_(m, g, t) : t;
+              gc = pick(gc, t, bit << k);
+              if ((int)(fr >> 32) < 0) {
+                t = fma_(c[k], g, t);
+              } else if (k > 0) {
+                const R m = (int)(up >> 32) < 0 ? mu : -mu;
+                t = pick(t, fma_(m, g, t), bit);
               }
               fr <<= 1;
               up <<= 1;
-            };
-            friction(2, c2);
-            friction(1, c1);
-            const R g = lane_read(t, r);
-            gc = lane == r ? t : gc;
-            if ((long long)fr < 0) t = fma_(c0, g, t);
-            fr <<= 1;
-            up <<= 1;
+            }
+            bit >>= 3;
+          };
+          for (int r = Rn - 3;;) {
+            load(cb3);
+            contact(ca3, r);
+            if ((r -= 3) < nlim) break;
+            load(ca3);
+            contact(cb3, r);
+            if ((r -= 3) < nlim) break;
           }
         } else {
           fr <<= 63 - max(Rn - 1, 0);
         }
-        R a0 = arow[max(nlim - 1, 0)];
-        for (int r = nlim - 1; r >= 0; --r) {
-          const R c0 = a0;
-          a0 = arow[max(r - 1, 0)];
-          asm volatile("" ::: "memory");
-          const R g = lane_read(t, r);
-          gc = lane == r ? t : gc;
-          if ((long long)fr < 0) t = fma_(c0, g, t);
-          fr <<= 1;
+        if (nlim > 0) {
+          unsigned long long bit = 1ull << (nlim - 1);
+          R a0 = arow[nlim - 1];
+          for (int r = nlim - 1; r >= 0; --r, bit >>= 1) {
+            const R c0 = a0;
+            a0 = arow[r - 1];
+            asm volatile("" ::: "memory");
+            const R g = lane_read(t, r);
+            gc = pick(gc, t, bit);
+            if ((int)(fr >> 32) < 0) t = fma_(c0, g, t);
+            fr <<= 1;
+          }
         }
         t -= gc;
         ybar = own && free_own ? fma_(-ia, gc, ybar) : ybar;
