@@ -885,11 +885,6 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       S->fused_dense = S->fused_dense && T.dense;
       S->fused_nc = std::max(S->fused_nc, T.nc);
     }
-    if (S->fused_dense)  // every type in the largest one's size class
-      for (TypeDev& T : S->types) {
-        T.dl = make_dense_layout(models[T.model]->info, dense_fixed_words(S->fused_nc));
-        T.lds_bytes = (size_t)T.dl.total * elem_size;
-      }
     for (int k : order) {
       const TypeDev& T = S->types[k];
       const int epw = kTeam / T.team;
@@ -906,7 +901,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
         (S->fused_lds <= 64 * 1024 || (err = set_fused_lds_limit(p->compute_fp64, S->fused_team, S->fused_lds)) == hipSuccess) &&
         (err = S->fused_dense ? dense_fused_blocks_per_cu(S->fused_nc, p->solver == AGS_SOLVER_TGS, S->fused_lds, &per_cu)
                               : fused_blocks_per_cu(p->compute_fp64, S->fused_team, S->fused_lds, &per_cu)) == hipSuccess &&
-        (err = hipMalloc(&S->units, units.size() * sizeof(int))) == hipSuccess &&
+        (err = hipMalloc(&S->units, (units.size() + 1) * sizeof(int))) == hipSuccess &&
         (err = hipMemcpy(S->units, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice)) == hipSuccess) {
       S->fused_grid = std::max(1, std::min(S->n_units, cus * std::max(1, per_cu)));
       S->fused_ok = true;
@@ -1035,6 +1030,7 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
     t.m = T.dm;
     t.lds = T.lds;
     t.dl = T.dl;
+    t.nc = T.nc;
     t.env_list = T.env_list;
     t.n_envs = T.n_envs;
     t.scratch = T.scratch;
@@ -1047,8 +1043,10 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
     for (size_t k = 0; k < S->types.size(); ++k) f.types[k] = type_args(S->types[k]);
     f.units = S->units;
     f.n_units = S->n_units;
-    hipError_t e = S->fused_dense
-                       ? launch_dense_fused(f, S->fused_nc, S->fused_grid, S->fused_lds, (hipStream_t)stream)
+    f.taken = S->units + 2 * S->n_units;
+    hipError_t e = S->fused_dense ? launch_zero_count(f.taken, (hipStream_t)stream) : hipSuccess;
+    if (e == hipSuccess)
+      e = S->fused_dense ? launch_dense_fused(f, S->fused_nc, S->fused_grid, S->fused_lds, (hipStream_t)stream)
                        : launch_step_fused(f, S->fused_grid, S->fused_lds, p.compute_fp64, S->fused_team, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "step: launch");
     return AGS_OK;

@@ -86,6 +86,7 @@ struct TypeArgs {
   DevModel m;
   Lds lds;
   DenseDyn dl;
+  int nc;                  // size class of the dense step
   const int* env_list;
   int n_envs;
   void* scratch;           // per env: J rows then W rows, r_cap x n_v each, in the compute type, then (64 lanes per
@@ -143,6 +144,7 @@ struct FusedArgs {
   TypeArgs types[kMaxFusedTypes];
   const int* units;  // 2 ints per unit: type, group
   int n_units;
+  int* taken;        // (dense) units taken beyond each workgroup's first, zero at the launch
 };
 hipError_t launch_step_fused(const FusedArgs& a, int grid, size_t lds_bytes, int fp64, int team, hipStream_t stream);
 hipError_t set_fused_lds_limit(int fp64, int team, size_t bytes);
