@@ -10,8 +10,7 @@ constexpr int kDenseMaxV = 31;      // columns: one lane each below 32, and one 
 constexpr int kDenseMaxLinks = 32;  // links: one lane and one mask bit each
 constexpr int kDenseRows = 64;      // rows solved one per lane; more go through global scratch
 constexpr int kDenseChunk = 32;     // rows whose Jacobian columns are formed at a time
-constexpr int kDenseLdsRows = 32;   // rows whose Delassus matrix is kept in LDS
-constexpr int kDenseAStride = 33;   // its row stride (odd: its transposed tile is written without bank conflicts)
+constexpr int kDenseLdsRows = 32;   // rows whose Delassus matrix is kept in LDS (small batches: kDenseRows)
 constexpr int kDenseXStride = 17;   // words per link of the subtree sums (10 inertia, 6 force; odd: no bank conflicts)
 constexpr int kDensePose = 7;       // words per link pose: quaternion xyzw, origin
 
@@ -26,7 +25,7 @@ constexpr int kDenseContacts = 21;  // contacts of an environment whose rows fit
 
 // Offsets in 8-byte words, except the integer arrays (t_*, lrow, rm, clk), which are in ints.  The overlays keep a
 // workgroup at 10-15 KB, so that the registers and not the LDS bound how many fit a CU.
-template <int NC>
+template <int NC, int LR = kDenseLdsRows>
 struct DenseLds {
   static constexpr int max2(int a, int b) { return a > b ? a : b; }
   // model masks: ancestors of a link, columns moving a link, columns of a row of M
@@ -41,12 +40,13 @@ struct DenseLds {
                        rm = 2 * X, co = X + 64, cn = X + 128, cx = cn + 66, cphi = cx + 66, clk = 2 * (cphi + 22),
                        lbias = cphi + 34,
                        x_words = max2(max2(kDenseXStride * NC, NC * (NC + 1) / 2 + 64), 128 + 66 + 66 + 34 + 64);
-  // The Delassus matrix of at most kDenseLdsRows rows overlays the region from its start, after the sweeps the impulses
+  // The Delassus matrix of at most LR rows (row stride odd: its transposed tile is written without bank conflicts) overlays the region from its start, after the sweeps the impulses
   // and the velocity change in the factor's columns.  G: pairs of columns of the factor's inverse transpose, column pair
   // m as (2 m + 2) x 2 words, behind the Delassus matrix (over the tail of X, written when the mass matrix has been read).
-  static constexpr int A = S, lam = A, u = A + kDenseRows, G = A + kDenseLdsRows * kDenseAStride,
+  static constexpr int A = S, lam = A, u = A + kDenseRows, A_stride = LR + 1, G = A + LR * A_stride,
                        g_words = NC / 2 * (NC / 2 + 1) * 2;
-  static constexpr int fixed = max2(X + x_words, G + g_words);  // then the model's root states
+  // (the sweeps read up to three rows behind the matrix) then the model's root states
+  static constexpr int fixed = max2(max2(X + x_words, G + g_words), A + (LR + 3) * A_stride);
   static_assert(S % 2 == 0 && V % 2 == 0 && co % 2 == 0 && u % 2 == 0 && G % 2 == 0, "16-byte aligned pairs");
   static_assert(kDensePose * NC + 6 * NC >= 6 * kDenseChunk && 6 * NC >= 64, "overlaid arrays fit");
   static_assert(lbias + 64 <= G, "the factor's columns leave what is read after them alone");
@@ -59,8 +59,12 @@ struct DenseDyn {
 inline DenseDyn make_dense_layout(const ags_model_info& info, int fixed_words) {
   return {fixed_words, (fixed_words + 13 * info.n_actors + 1) & ~1};
 }
+template <int LR>
 inline int dense_fixed_words(int nc) {
-  return nc == 16 ? DenseLds<16>::fixed : nc == 28 ? DenseLds<28>::fixed : DenseLds<32>::fixed;
+  return nc == 16 ? DenseLds<16, LR>::fixed : nc == 28 ? DenseLds<28, LR>::fixed : DenseLds<32, LR>::fixed;
+}
+inline int dense_fixed_words(int nc, int lds_rows) {
+  return lds_rows == kDenseRows ? dense_fixed_words<kDenseRows>(nc) : dense_fixed_words<kDenseLdsRows>(nc);
 }
 inline int dense_x_words(int nc) {
   return nc == 16 ? DenseLds<16>::x_words : nc == 28 ? DenseLds<28>::x_words : DenseLds<32>::x_words;

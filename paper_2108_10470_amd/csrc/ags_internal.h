@@ -214,8 +214,8 @@ hipError_t launch_scale_by_kp(float* x, const float* kp, int n, hipStream_t stre
 
 hipError_t launch_step(const StepArgs& a, int n_envs, int fp64, int team, hipStream_t stream);
 // the dense form of the FP64 step with one environment per wavefront (TypeArgs::dl), and its persistent launch
-// (nc: the size class, at least dense_class of every model)
-hipError_t launch_dense(const StepArgs& a, int nc, int n_envs, size_t lds_bytes, hipStream_t stream);
+// (nc: the size class, at least dense_class of every model; lds_rows: kDenseLdsRows or kDenseRows)
+hipError_t launch_dense(const StepArgs& a, int nc, int lds_rows, int n_envs, size_t lds_bytes, hipStream_t stream);
 hipError_t launch_dense_fused(const FusedArgs& a, int nc, int grid, size_t lds_bytes, hipStream_t stream);
 hipError_t dense_fused_blocks_per_cu(int nc, int tgs, size_t lds_bytes, int* blocks);
 // reorders the env ids order[0, n) by rows[env], most first (tmp: order_tmp_ints(n) ints)

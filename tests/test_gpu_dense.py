@@ -51,9 +51,25 @@ def swing(n: int) -> W.EnvSpec:
 ], ids=lambda x: f"{x.name}{x.n_v}" if isinstance(x, W.EnvSpec) else str(x))
 @pytest.mark.parametrize("solver", [0, 1], ids=["pgs", "tgs"])
 def test_dense_step_edges_match_oracle(env, rows, solver):
+    check(env, rows, solver, 1)
+
+
+@pytest.mark.parametrize("env, rows", [(caterpillar(5), 15), (caterpillar(11), 33), (caterpillar(20), 60), (caterpillar(22), 66),
+                                       (caterpillar(26), 78), (boxes(5), 60)],
+                         ids=lambda x: f"{x.name}{x.n_v}" if isinstance(x, W.EnvSpec) else str(x))
+@pytest.mark.parametrize("solver", [0, 1], ids=["pgs", "tgs"])
+def test_dense_step_large_batch_matches_oracle(env, rows, solver):
+    """More than four environments per CU: up to 32 rows in LDS, more streamed from scratch."""
+    check(env, rows, solver, 40)
+
+
+def check(env, rows, solver, copies):
     p = W.SimParams(solver=solver, pgs_iters=5)
     oe, root, dof, act = PT.oracle_states(env, p, n_envs=6, n_steps=9, every=2)
+    root, dof, act = (np.tile(x, (copies,) + (1,) * (x.ndim - 1)) for x in (root, dof, act))
     g, o = PT.run(env, p, root, dof, act, oe=oe, fp64=True)
+    for k in ("root", "dof", "contact_force"):  # copies of an environment give the same bits
+        assert (g[k].reshape(copies, -1) == g[k].reshape(copies, -1)[0]).all(), k
     s = PT.summarize(PT.compare(env, p, g, o))
     print(env.name, env.n_v, "max rows", int(o["row_count"].max()), s)
     assert o["row_count"].max() >= rows
