@@ -58,12 +58,22 @@ __global__ __launch_bounds__(64) void dense_jacmass_kernel(JacMassArgs) {
         for (int q = 0; q < 10; ++q) w[q] *= f;
       }
     }
+    // links with non-finite terms stay out of the products with 0/1 matrices (0 x NaN); the sums they belong to get NaN
+    R off = R(0);
+#pragma unroll
+    for (int q = 0; q < 10; ++q) off += R(0) * w[q];
+    const unsigned bad = (unsigned)__ballot(!(off == R(0)));
     if (lane < NC) {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) X[kDenseXStride * lane + q] = w[q];
+      for (int q = 0; q < 16; ++q) X[kDenseXStride * lane + q] = (bad >> lane) & 1u ? R(0) : w[q];
     }
     wsync();
     subtree_sum<NC>(X, la, lane, X, la, 0);
+    for (unsigned m = bad; m; m &= m - 1) {
+      const int above = la[__ffs(m) - 1];
+      if (lane < NC && ((above >> lane) & 1)) X[kDenseXStride * lane] = X[kDenseXStride * lane + 1] = R(NAN);
+      wsync();
+    }
     if (lane < NC) st6(Fm + 6 * lane, comp_mul(X + kDenseXStride * cl.link(), ld6(S + 6 * lane)));
     wsync();
     mass_matrix<NC>(Fm, S, ccm, X, lane);

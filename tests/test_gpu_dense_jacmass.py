@@ -28,3 +28,17 @@ def test_dense_jacobian_and_mass_edges_match_oracle(env):
     sim.bind(ags.BODY_MASS_SCALE, torch.full(sim.shapes[ags.BODY_MASS_SCALE], 2.0, dtype=torch.float32, device=sim.device))
     J2, M2 = JM._gpu(sim, 0, root, dof)
     assert (J2 == J).all() and (M2 == 2 * M).all()
+
+
+def test_non_finite_links_spoil_only_their_own_entries():
+    """A joint angle that is not finite: the Jacobian rows and mass-matrix entries that do not depend on it are unchanged."""
+    env = W.as_f32(W.env_arm_box())
+    root, dof = JM._poses(env, 2, 3)
+    dof[1, 2, 0] = np.nan  # the third joint of the arm
+    sim = ags.Sim([ags.Model(env)], [0] * 2, W.params_f32(W.SimParams()))
+    root[1], dof[1, [0, 1]], dof[1, 3:] = root[0], dof[0, [0, 1]], dof[0, 3:]
+    J, M = JM._gpu(sim, 0, root, dof)
+    box = slice(env.n_v - 6, env.n_v)
+    assert np.isfinite(J[0]).all() and np.isfinite(M[0]).all()
+    assert (M[1][box, box] == M[0][box, box]).all() and (J[1][-1] == J[0][-1]).all()
+    assert (M[1][box, :env.n_v - 6] == 0).all() and np.isnan(M[1][2, 2])
