@@ -34,9 +34,11 @@ BYTES_PER_ENV_STEP = 764.0
 PEAK_VALU_TFLOPS = 78.6   # 256 CU x 4 SIMD x 16 lanes x 2 flop x 2.4 GHz (FP32 unpacked == FP64 vector)
 PEAK_HBM_GBS = 8000.0
 CSRC = os.path.join(ROOT, "paper_2108_10470_amd", "csrc")
-PROFILES = {"step": (os.path.join(ROOT, "profiles", "step_kernel_humanoid4096.md"), ("ags_step.hip", "ags_internal.h")),
+_DENSE = ("ags_dense_ops.h", "ags_dense_layout.h", "ags_vec.h", "ags_internal.h")
+PROFILES = {"step": (os.path.join(ROOT, "profiles", "step_kernel_humanoid4096.md"),
+                     ("ags_dense.hip", "ags_step.hip") + _DENSE),
             "adjoint": (os.path.join(ROOT, "profiles", "adjoint_kernel_humanoid4096.md"),
-                        ("ags_adjoint.hip", "ags_internal.h"))}
+                        ("ags_dense_adjoint.hip", "ags_adjoint.hip", "ags_adj_math.h") + _DENSE)}
 
 
 def measured_traffic(variant, kernel="step"):
@@ -666,7 +668,7 @@ def main():
                    "mean_rows_per_substep_steps_0_to_%d" % args.rows_ref_steps: rows_ref},
         "roofline": {"bound": "alu", "achieved": ach_tf, "peak": PEAK_VALU_TFLOPS, "unit": "TFLOP/s",
                      "frac": None if ach_tf is None else ach_tf / PEAK_VALU_TFLOPS, "traffic": measured_traffic(head),
-                     "kernel": "step_kernel<double>" if head == "fp64" else "step_kernel<float>",
+                     "kernel": "dense_kernel<28>" if head == "fp64" else "step_kernel<float>",
                      "launch_ms": t_launch * 1e3,
                      "hbm": {"achieved": ach_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ach_gbs / PEAK_HBM_GBS,
                              "bytes_per_env_step": BYTES_PER_ENV_STEP},

@@ -14,6 +14,14 @@
 //   * every adjoint of a column's axis, a link's inertia or a contact's point and direction is a sum over the columns
 //     moving a link, the columns or links below a column, or the rows on it: products with the same 0/1 matrices.
 //     <s, I y> terms of all columns over a link need only sum(w_s w_y^T + w_y w_s^T) and sum(v_y x w_s + v_s x w_y).
+//
+// What bounds it: the chain of one wavefront's dependent instructions, with 1.5 wavefronts per SIMD resident (six
+// workgroups of 26 KB per CU for the humanoid-like model with room for 32 rows, 256 registers; four of 34 KB and 385
+// registers were slower), and after it the few environments with more rows, in a form with room for 64 (44 of 4096
+// take 0.27 ms on their own).  Cycles per environment and call, 4096 of them, three recomputations and two reversals:
+// 400 k; recomputation outside Gauss-Seidel 160 k, Gauss-Seidel 60 k and its reverse 45 k, products 37 k, mass-matrix
+// terms with the kinematics formed again 27 k, rows 17 k, RNEA 20 k, integration and solves 26 k.
+// 4096 humanoid-like environments 0.84 ms per call (general form 4.7), relative difference 1e-13.
 #include "ags_dense_ops.h"
 #include "ags_adj_math.h"
 
