@@ -9,6 +9,7 @@ namespace ags {
 constexpr int kDenseMaxV = 31;      // columns: one lane each below 32, and one more lane for the right-hand side
 constexpr int kDenseMaxLinks = 32;  // links: one lane and one mask bit each
 constexpr int kDenseRows = 64;      // rows solved one per lane; more go through global scratch
+constexpr int kDenseZWords = 32 * kDenseRows;  // tiles of Z^T of up to 64 rows in scratch
 constexpr int kDenseChunk = 32;     // rows whose Jacobian columns are formed at a time
 constexpr int kDenseLdsRows = 32;   // rows whose Delassus matrix is kept in LDS (small batches: kDenseRows)
 constexpr int kDenseXStride = 17;   // words per link of the subtree sums (10 inertia, 6 force; odd: no bank conflicts)

@@ -832,7 +832,10 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       return hip_fail(err, "sim: adjoint LDS limit");
     }
     // J and W rows (slow path), then the wide path's columns of A (one entry per lane of a 64-lane team)
-    T.scratch_stride = 2ll * D.r_cap * std::max(1, D.n_v) + (T.team == 64 ? 64ll * 64 : 0) + (T.dense ? 32ll * 64 + 3ll * D.r_cap + 8ll * D.n_slots : 0);
+    T.scratch_stride = 2ll * D.r_cap * std::max(1, D.n_v) + (T.team == 64 ? 64ll * 64 : 0);
+    if (T.dense) {  // tiles of Z^T in the words of J and W, columns of A, row tables, contacts
+      T.scratch_stride = std::max(2ll * D.r_cap * D.n_v, (long long)kDenseZWords) + 64ll * 64 + 3ll * D.r_cap + 8ll * D.n_slots;
+    }
     T.scratch_stride = (T.scratch_stride + 63) & ~63ll;
     if (T.team == 64) {
       if ((err = hipMalloc(&T.step_order, sizeof(int) * (T.n_envs + order_tmp_ints(T.n_envs)))) != hipSuccess ||
@@ -843,10 +846,11 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       }
       T.order_tmp = T.step_order + T.n_envs;
     }
+    // (1024: the streamed columns of A are read up to 13 rows past the matrix)
     const size_t elem = p->compute_fp64 ? sizeof(double) : sizeof(float);
     const int epw = kTeam / T.team;
     const size_t padded = (size_t)((T.n_envs + epw - 1) / epw) * epw;
-    if ((err = hipMalloc(&T.scratch, (size_t)T.scratch_stride * padded * elem)) != hipSuccess) {
+    if ((err = hipMalloc(&T.scratch, ((size_t)T.scratch_stride * padded + 1024) * elem)) != hipSuccess) {
       S->types.push_back(T);
       ags_sim_destroy(S);
       return hip_fail(err, "sim: scratch");
