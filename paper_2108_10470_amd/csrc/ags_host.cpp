@@ -1067,14 +1067,15 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
   // past 32 take the chunked response path): one-env-per-wavefront types dispatch their envs in order of
   // the rows of their previous step, most first, so that the likely slow ones start in the first round of
   // workgroups.  The order changes no result: every env is computed on its own.  A batch whose workgroups all start at
-  // once has no use for it (dense step: eight workgroups per CU; 64 ants 47 us with the ordering launch, 41 without).
+  // once (eight wavefronts per CU where the LDS holds them) has no use for it (64 ants 47 us with the ordering launch, 41
+  // without).
   a.env_rows = S->env_rows;
   for (TypeDev& T : S->types) {
     a.ty = type_args(T);
     if (T.step_order) a.ty.env_list = T.step_order;
     hipError_t e = T.dense ? launch_dense(a, T.nc, T.lds_rows, T.n_envs, T.lds_bytes, (hipStream_t)stream)
                            : launch_step(a, T.n_envs, p.compute_fp64, T.team, (hipStream_t)stream);
-    if (e == hipSuccess && T.step_order && !(T.dense && T.n_envs <= 8 * S->n_cu))
+    if (e == hipSuccess && T.step_order && T.n_envs > S->n_cu * std::min(8, (int)(160 * 1024 / T.lds_bytes)))
       e = launch_order_by_rows(T.step_order, T.order_tmp, S->env_rows, T.n_envs, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "step: launch");
   }

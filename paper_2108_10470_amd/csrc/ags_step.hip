@@ -600,7 +600,7 @@ __device__ __forceinline__ void step_group(const StepArgs& P, const TypeArgs& T,
   const int n_envs = T.n_envs;
   constexpr int EPW = kTeam / TEAM;  // environments per wavefront
   constexpr int FR = kFastRows;      // rows of the register Gauss-Seidel path and of one response chunk
-  constexpr int kWideAhead = 8;      // wide path: rows of A columns in flight ahead of the Gauss-Seidel updates
+  constexpr int kWideAhead = 12;     // wide path: rows of A columns in flight ahead of the Gauss-Seidel updates
   static_assert(FR <= TEAM, "fast rows exceed the lanes of an environment");
   const int t = threadIdx.x;         // lane in the wavefront
   const int tm = EPW == 1 ? 0 : t / TEAM;  // team (environment slot) of this lane
@@ -1481,39 +1481,64 @@ __device__ __forceinline__ void step_group(const StepArgs& P, const TypeArgs& T,
       R lam = R(0), hi = fric ? R(0) : R(kOpenBound), lo = R(0), bia = bias * ia;
       R c = -bia;
       const R hstep = h / R(max(P.iters, 1));
-      const R* const acol = Ag + tt;
-      for (int it = 0; it < P.iters; ++it) {
-        if (tgs && it > 0 && own && !fric) {
+      // (buffer loads with scalar offsets: with vector addresses a chunk waited for the loads of the one before, whose
+      // destinations its addresses reused, and an update took 209 cycles.  Lanes and rows past the last row read what is
+      // in the scratch words there, which nothing uses)
+      const int Rw = __builtin_amdgcn_readfirstlane(Rn), iters = P.iters;
+      const unsigned long long at_ag = (unsigned long long)Ag;
+      const unsigned long long ag = (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)at_ag) |
+                                    (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(at_ag >> 32)) << 32;
+      constexpr int kColumn = TEAM * (int)sizeof(R);
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)ag, 0, (TEAM + kWideAhead) * kColumn, 0x00027000);
+      auto load = [&](R* b, int r0) {
+#pragma unroll
+        for (int q = 0; q < kWideAhead; ++q) {
+          if constexpr (sizeof(R) == 4) {
+            b[q] = __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(rsrc, tt * 4, (r0 + q) * kColumn, 0));
+          } else {
+            const auto w = __builtin_amdgcn_raw_buffer_load_b64(rsrc, tt * 8, (r0 + q) * kColumn, 0);
+            b[q] = __hiloint2double((int)w[1], (int)w[0]);
+          }
+        }
+        asm volatile("" ::: "memory");
+      };
+      auto update = [&](const R* b, int r0) {
+#pragma unroll
+        for (int q = 0; q < kWideAhead; ++q) {
+          const int r = r0 + q;
+          if (r < Rw) {
+            const R cand = clamp_(fma_(-y, ia, c), lo, hi);
+            const R dl = lane_read(cand - lam, r);
+            lam = tt == r ? cand : lam;
+            c = lam - bia;
+            hi = fma_(nrmv == r ? mu : R(0), dl, hi);
+            lo = -(hi * fsign);
+            y += b[q] * dl;
+          }
+        }
+      };
+      R b0[kWideAhead], b1[kWideAhead];
+      int r0 = 0, it = 0;  // first row and sweep of the next update
+      auto next = [&]() {
+        r0 += kWideAhead;
+        if (r0 < Rw) return;
+        r0 = 0;
+        if (tgs) pos += hstep * y;
+        if (++it < iters && tgs && own && !fric) {
           bias = row_bias(pos, h, R(P.beta));
           bia = bias * ia;
           c = lam - bia;
         }
-        R nx[kWideAhead];
-#pragma unroll
-        for (int q = 0; q < kWideAhead; ++q) nx[q] = own && q < Rn ? acol[q * TEAM] : R(0);
-        for (int r0 = 0; r0 < Rn; r0 += kWideAhead) {
-          R cur[kWideAhead];
-#pragma unroll
-          for (int q = 0; q < kWideAhead; ++q) {
-            cur[q] = nx[q];
-            const int rn = r0 + kWideAhead + q;
-            nx[q] = own && rn < Rn ? acol[rn * TEAM] : R(0);  // lanes without a row read nothing
-          }
-#pragma unroll
-          for (int q = 0; q < kWideAhead; ++q) {
-            const int r = r0 + q;
-            if (r < Rn) {
-              const R cand = clamp_(fma_(-y, ia, c), lo, hi);
-              const R dl = team_read<TEAM>(tm, cand - lam, r);
-              lam = tt == r ? cand : lam;
-              c = lam - bia;
-              hi = fma_(nrmv == r ? mu : R(0), dl, hi);
-              lo = -(hi * fsign);
-              y += cur[q] * dl;
-            }
-          }
-        }
-        if (tgs) pos += hstep * y;
+      };
+      load(b0, 0);
+      while (it < iters) {
+        load(b1, r0 + kWideAhead < Rw ? r0 + kWideAhead : 0);
+        update(b0, r0);
+        next();
+        if (it >= iters) break;
+        load(b0, r0 + kWideAhead < Rw ? r0 + kWideAhead : 0);
+        update(b1, r0);
+        next();
       }
       if (own) s.rlam[tt] = lam;
       __syncthreads();
