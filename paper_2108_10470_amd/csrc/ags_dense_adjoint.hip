@@ -18,10 +18,13 @@
 // What bounds it: the chain of one wavefront's dependent instructions, with 1.5 wavefronts per SIMD resident (six
 // workgroups of 26 KB per CU for the humanoid-like model with room for 32 rows, 256 registers; four of 34 KB and 385
 // registers were slower), and after it the few environments with more rows, in a form with room for 64 (44 of 4096
-// take 0.27 ms on their own).  Cycles per environment and call, 4096 of them, three recomputations and two reversals:
-// 400 k; recomputation outside Gauss-Seidel 160 k, Gauss-Seidel 60 k and its reverse 45 k, products 37 k, mass-matrix
-// terms with the kinematics formed again 27 k, rows 17 k, RNEA 20 k, integration and solves 26 k.
-// 4096 humanoid-like environments 0.84 ms per call (general form 4.7), relative difference 1e-13.
+// take 0.25 ms on their own).  Cycles per environment and call, 4096 of them, three recomputations and two reversals:
+// 392 k; recomputation outside Gauss-Seidel 157 k, Gauss-Seidel 65 k and its reverse 40 k, products 37 k, mass-matrix
+// terms with the kinematics formed again 27 k, rows 17 k, RNEA 20 k, integration and solves 30 k.
+// A lone wavefront issues an instruction about every seven cycles, so the sweeps are counted in instructions, scalar
+// ones and branches included: impulses taken from the captured z after a sweep instead of selected row by row, and a
+// reverse without branches, took the 52-60 row environment from 637 k to 599 k cycles.
+// 4096 humanoid-like environments 0.81 ms per call (general form 4.7), relative difference 1e-13.
 #include "ags_dense_ops.h"
 #include "ags_adj_math.h"
 
@@ -511,7 +514,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       unsigned long long bit = 1;
       auto apply = [&](R cand, R a, int r, unsigned long long at) {
         zc = pick(zc, z, at);
-        row_apply(z, rlam, cand, a, r, at);
+        z = fma_(a, lane_read(cand - rlam, r), z);
       };
       // (columns past the last row are read within the workgroup's LDS and not used)
       Lp<R> acol = A_ + kk;
@@ -547,6 +550,12 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
           contact(cb3, r);
           if ((r += 3) >= Rn) break;
         }
+      }
+      // a row is updated once a sweep: its new impulse is its captured z within its bounds
+      {
+        const R n = clamp_low0(zc), m = mu * __shfl(n, fric ? lane - (kind - 3) : lane, 64);
+        const R f = __builtin_fmin(__builtin_fmax(zc, -m), m);
+        rlam = fric ? f : n;
       }
       if (reverse) {
         const unsigned long long fr = __ballot(zc == rlam), up = __ballot(zc > rlam);
@@ -701,19 +710,19 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
             asm volatile("" ::: "memory");
           };
           auto contact = [&](const R* c, int r) {
+            // a clamped friction row moves its normal's lane alone, by +-mu, a clamped normal none: no branches
+            const R mn = pick(R(0), mu, bit);
 #pragma unroll
             for (int k = 2; k >= 0; --k) {
               const R g = lane_read(t, r + k);
               gc = pick(gc, t, bit << k);
-              if ((int)(fr >> 32) < 0) {
-                t = fma_(c[k], g, t);
-              } else if (k > 0) {
-                const R m = (int)(up >> 32) < 0 ? mu : -mu;
-                t = pick(t, fma_(m, g, t), bit);
-              }
-              fr <<= 1;
-              up <<= 1;
+              const unsigned long long on = (unsigned long long)((long long)(fr << (2 - k)) >> 63);
+              const int neg = ~(int)(up >> 32) << (2 - k) & (int)0x80000000;
+              const R m = k > 0 ? __hiloint2double(__double2hiint(mn) ^ neg, __double2loint(mn)) : R(0);
+              t = fma_(pick(m, c[k], on), g, t);
             }
+            fr <<= 3;
+            up <<= 3;
             bit >>= 3;
           };
           for (int r = Rn - 3;;) {
