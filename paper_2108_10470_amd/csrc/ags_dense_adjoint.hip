@@ -554,8 +554,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       // a row is updated once a sweep: its new impulse is its captured z within its bounds
       {
         const R n = clamp_low0(zc), m = mu * __shfl(n, fric ? lane - (kind - 3) : lane, 64);
-        const R f = __builtin_fmin(__builtin_fmax(zc, -m), m);
-        rlam = fric ? f : n;
+        rlam = fric ? clamp_symv(zc, m) : n;
       }
       if (reverse) {
         const unsigned long long fr = __ballot(zc == rlam), up = __ballot(zc > rlam);
