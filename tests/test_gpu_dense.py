@@ -63,8 +63,16 @@ def test_dense_step_large_batch_matches_oracle(env, rows, solver):
     check(env, rows, solver, 40)
 
 
-def check(env, rows, solver, copies):
-    p = W.SimParams(solver=solver, pgs_iters=5)
+@pytest.mark.parametrize("iters", [0, 1, 2])
+@pytest.mark.parametrize("env, rows", [(caterpillar(10), 30), (boxes(1), 12), (swing(8), 0)],
+                         ids=lambda x: f"{x.name}{x.n_v}" if isinstance(x, W.EnvSpec) else str(x))
+def test_dense_step_few_sweeps_match_oracle(env, rows, iters):
+    """No sweep, only the one that keeps the rows' values, and one before it."""
+    check(env, rows, 0, 1, iters)
+
+
+def check(env, rows, solver, copies, iters=5):
+    p = W.SimParams(solver=solver, pgs_iters=iters)
     oe, root, dof, act = PT.oracle_states(env, p, n_envs=6, n_steps=9, every=2)
     root, dof, act = (np.tile(x, (copies,) + (1,) * (x.ndim - 1)) for x in (root, dof, act))
     g, o = PT.run(env, p, root, dof, act, oe=oe, fp64=True)
