@@ -105,7 +105,7 @@ struct ags_model {
   std::vector<unsigned long long> link_anc, col_anc;  // ancestor bit masks (links; generalized columns)
   std::vector<int> col_link;                           // owning link of each generalized column
   std::vector<int> link_cols, jump;                    // dense step: columns moving a link, pointer-jumping table
-  int n_jump = 0;
+  int n_jump = 0, n_parts = 0;
   bool body_pairs = false;                             // has sphere/capsule-vs-box pairs
   int max_joint_entries = 0;  // most revolute/prismatic joints on the paths of one slot's two bodies
   std::vector<float> mass, com, inertia;
@@ -340,6 +340,11 @@ extern "C" int ags_model_create(const ags_actor_desc* actors, int32_t n_actors, 
       for (size_t b = 0; b < a; ++b) m |= 1ull << own[b];
       M->col_anc[own[a]] = m;
     }
+  }
+  for (int i = 0; i < nl; ++i) {
+    const int p = M->li[i * LI_COLS + LI_PARENT];
+    if (p < 0) M->n_parts += M->li[i * LI_COLS + LI_ROOTCOL] >= 0 || n_actors > 1;
+    else M->n_parts += M->li[p * LI_COLS + LI_PARENT] < 0 && M->li[p * LI_COLS + LI_ROOTCOL] < 0;
   }
   M->link_cols.assign(nl, 0);
   M->jump.assign(nl, 0);
@@ -793,6 +798,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     D.link_cols = (const int*)(b + offs[19]);
     D.jump = (const int*)(b + offs[20]);
     D.n_jump = M->n_jump;
+    D.n_parts = M->n_parts;
     T.body_pairs = M->body_pairs;
     const int adj_cap = p->adjoint_max_rows > 0 ? p->adjoint_max_rows : kAdjRows;
     const int adj_small_cap = std::min(adj_cap, kAdjSmallRows);

@@ -73,6 +73,7 @@ struct DevModel {
   const int* link_cols;
   const int* jump;
   int n_jump;
+  int n_parts;  // independent parts: trees of free roots, branches of fixed bases, and a base itself beside other actors
   // fixed tendons: n_tj tendon joints (4 ints each: tendon, DOF, column, parent joint or -1; coefficient),
   // 6 doubles per tendon (stiffness, damping, rest length, lower, upper, limit stiffness)
   int n_tj;
