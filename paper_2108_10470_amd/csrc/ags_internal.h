@@ -14,6 +14,7 @@ constexpr int kMaxLinks = 64;
 constexpr int kMaxV = 64;       // generalized velocities per environment (one lane each in the solver)
 constexpr int kMaxSlots = 256;
 constexpr float kMinRowMass = 1e-6f;  // rows with J M~^-1 J^T below this are dropped (immovable)
+constexpr double kMinRootPivot = 1e-30;  // least pivot of a free root's inertia (a body without mass keeps its velocity)
 constexpr int kPhases = 10;           // controls, forward, inward, outward, v*, narrow, rows, responses, PGS, outputs
 constexpr int kJointEntries = 10;     // joint (non-root) entries of a compact Jacobian row
 constexpr int kFastRows = 32;         // rows solved in registers (one per lane); also the row-response chunk

@@ -178,7 +178,7 @@ __device__ __forceinline__ void chol6(const SI<R>& K, const P& L, const P& dinv)
     R d = si_at(K, j, j);
 #pragma unroll
     for (int k = 0; k < j; ++k) d -= L[j * (j + 1) / 2 + k] * L[j * (j + 1) / 2 + k];
-    d = sqrt_(max_(d, R(1e-30)));
+    d = sqrt_(max_(d, R(kMinRootPivot)));
     L[j * (j + 1) / 2 + j] = d;
     R inv = R(1) / d;
     dinv[j] = inv;

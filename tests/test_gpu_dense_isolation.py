@@ -7,6 +7,7 @@ torch = pytest.importorskip("torch")
 
 from paper_2108_10470_amd import ags, workloads as W
 from tests import parity as PT
+from tests.test_gpu_dense import boxes
 
 pytestmark = pytest.mark.gpu
 
@@ -132,3 +133,26 @@ def test_massless_branch_stays_alone(env, solver):
     sim.set_properties(mass_scale=torch.tensor(mass.reshape(-1), device="cuda:0"), damping=zero, stiffness=zero)
     sim.step()
     check_alone(env, results(sim, env), chains, parts, n)
+
+
+@pytest.mark.parametrize("env", [boxes(1), boxes(3), W.env_arm_box(), bare(W.env_ant())], ids=lambda e: f"{e.name}{e.n_v}")
+@pytest.mark.parametrize("solver", [0, 1], ids=["pgs", "tgs"])
+def test_massless_free_body_as_in_the_articulated_form(env, solver):
+    """Mass factor 0 on one free body (of the ant: its torso, the legs keep their mass): without force it keeps its velocity
+    and follows its contacts.  Reference: the articulated form (two environments per wavefront, FP64), parity tolerance."""
+    env, p = W.as_f32(env), W.params_f32(W.SimParams(solver=solver))
+    first = np.cumsum([0] + [len(a.links) for a in env.actors])
+    free = [k for k, a in zip(first, env.actors) if a.links[0].joint == "free"]
+    root, dof, act = states(env, p, len(free) + 1)
+    mass = np.ones((len(free) + 1, env.n_bodies), np.float32)
+    for e, k in enumerate(free, 1):
+        mass[e, k] = 0.0
+    outs = []
+    for lanes in (64, 32):
+        sim = make(env, p, root, dof, act, lanes_per_env=lanes)
+        sim.set_properties(mass_scale=torch.tensor(mass.reshape(-1), device="cuda:0"))
+        sim.step()
+        outs.append(results(sim, env))
+    for x, y in zip(outs[0][:5], outs[1][:5]):
+        assert np.isfinite(y).all() and (np.abs(x - y) <= PT.ATOL + PT.RTOL * np.abs(y)).all(), np.abs(x - y).max()
+    assert (outs[0][5] == outs[1][5]).all()
