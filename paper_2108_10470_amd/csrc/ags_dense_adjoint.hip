@@ -158,7 +158,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       kp = R(lf[LF_KP]);
       kd = R(lf[LF_KD]);
       tau = R(gp(P->act)[d]) + kp * (pt - qj[cl.dof()] - h * nu[lane]) + kd * (vt - nu[lane]);
-      arm = R(lf[LF_ARM]) + h * kd + h * h * kp;
+      arm = finite_armature(R(lf[LF_ARM]) + h * kd + h * h * kp);
     }
     // ---------------------------------------------------- poses, axes, velocities, velocity-product accelerations
     const auto lfl = gp(P->m.lf) + (lk.is() ? lane : 0) * LF_COLS;
