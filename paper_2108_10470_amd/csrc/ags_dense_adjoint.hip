@@ -500,6 +500,9 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       ia = ian == R(0) ? R(0) : ia;
     }
     R z = -(y + bias) * ia, rlam = R(0);
+    R zn = clamp_low0(z);  // formed where z is and not where it is used
+    R muv = mu;
+    asm("" : "+v"(muv));
     if (lane < RC)
 #pragma unroll 4
       for (int r = 0; r < Rn; ++r) {
@@ -524,14 +527,16 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
         acol += AS;
         a0 = acol[0];
         asm volatile("" ::: "memory");
-        apply(clamp_low0(z), a, r, bit);
+        apply(zn, a, r, bit);
+        zn = clamp_low0(z);
       }
       if (n_contacts > 0) {
         auto contact = [&](const R* c, int r) {
-          const R n = clamp_low0(z), m = lane_read(mu * n, r);
-          apply(n, c[0], r, bit);
+          const R m = muv * lane_read(zn, r);
+          apply(zn, c[0], r, bit);
           apply(clamp_sym(z, m), c[1], r + 1, bit << 1);
           apply(clamp_sym(z, m), c[2], r + 2, bit << 2);
+          zn = clamp_low0(z);
           bit <<= 3;
         };
         auto load = [&](R* c) {
@@ -554,7 +559,7 @@ __device__ __forceinline__ void dense_adjoint_env(Cp<AdjArgs> P_, int ei) {
       // a row is updated once a sweep: its new impulse is its captured z within its bounds
       {
         const R n = clamp_low0(zc), m = mu * __shfl(n, fric ? lane - (kind - 3) : lane, 64);
-        rlam = fric ? clamp_symv(zc, m) : n;
+        rlam = fric ? clamp_sym(zc, m) : n;
       }
       if (reverse) {
         const unsigned long long fr = __ballot(zc == rlam), up = __ballot(zc > rlam);
