@@ -1,5 +1,6 @@
-// LDS layout of the dense step kernel (one environment per 64-lane workgroup): plain C++ with no HIP
-// dependency, shared by the host runtime and the host-side layout checker of the tests.
+// LDS layouts of the dense step and adjoint kernels (one environment per 64-lane workgroup): plain C++ with no HIP
+// dependency, shared by the host runtime, the kernels and the host-side replay of the tests (dense_lds_check.cpp), which knows
+// the phases in which each array is alive.
 #pragma once
 
 #include "../../include/ags.h"

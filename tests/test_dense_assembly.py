@@ -1,8 +1,10 @@
 """The gfx950 assembly of the dense kernels (CPU only: compiled here, not run).
 
-The wait states that gfx950 asks for between a lane read and the write of its source, and between a vector instruction and the
+1. The wait states that gfx950 asks for between a lane read and the write of its source, and between a vector instruction and the
 lane read that wrote its scalar operand, are inserted by the compiler, and only for instructions that it knows: the kernels'
 inline assembly may order and hide values but must not hold instructions.
+2. LDS is reached through DS instructions only: no FLAT memory instruction and no call (the 64-row layouts lie partly beyond
+64 KiB of LDS; an earlier instrumented adjoint that reached such words through FLAT instructions faulted).
 """
 import os
 import re
@@ -40,3 +42,16 @@ def test_inline_assembly_holds_no_instructions(assembly, src):
         for block in re.findall(r";+#?ASMSTART\n(.*?);+#?ASMEND", body, flags=re.S):
             code = [line.split(";")[0].strip() for line in block.splitlines()]
             assert not any(code), (name, block)
+
+
+@pytest.mark.parametrize("src", sorted(SOURCES))
+def test_lds_is_reached_through_ds_instructions_only(assembly, src):
+    for name, body in kernels(assembly[src]).items():
+        assert not re.search(r"\bflat_(load|store|atomic)", body), name
+        assert "s_swappc" not in body and "s_call" not in body, name
+        lines = body.splitlines()
+        for n, line in enumerate(lines):  # an s_setpc may only end a long branch to a label of the kernel
+            if "s_setpc_b64" in line:
+                window = "\n".join(lines[max(0, n - 4):n])
+                assert "s_getpc_b64" in window and re.search(r"\(\.LBB\w+-\.Lpost_getpc\w*\)", window), (name, n)
+        assert re.search(r"\bds_(read|write)", body), name
