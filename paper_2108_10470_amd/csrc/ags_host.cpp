@@ -583,6 +583,13 @@ hipError_t noalloc_scratch_ptr(int dev, void** out) {
 }
 }  // namespace
 
+// One persistent launch over a list of (type, group) units
+struct FusedLaunch {
+  int* units = nullptr;  // device: pairs, then the count of those taken
+  int n_units = 0, grid = 0, team = 64, nc = 0;
+  size_t lds = 0;
+};
+
 struct ags_sim {
   ags_sim_params params{};
   int n_envs = 0;
@@ -614,11 +621,8 @@ struct ags_sim {
   hipStream_t aux2 = nullptr;
   hipEvent_t ev_big_start = nullptr, ev_big_done = nullptr, ev_big_listed = nullptr;
   // persistent (fused) launch
-  bool fused_ok = false, fused_dense = false;
-  int fused_nc = 0;
-  int* units = nullptr;  // device: (type, group) pairs
-  int n_units = 0, fused_grid = 0, fused_team = 64;
-  size_t fused_lds = 0;
+  bool fused_ok = false;
+  FusedLaunch fused[2];  // of the types without and with the dense form
 };
 
 namespace {
@@ -896,38 +900,37 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       return (nv * nv + 4.0 * T.dm.n_slots + 8.0 * T.dm.n_links) * (kTeam / T.team);
     };
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost(S->types[a]) > cost(S->types[b]); });
-    std::vector<int> units;
-    S->fused_lds = 0;
-    S->fused_dense = true;
-    for (const TypeDev& T : S->types) {
-      S->fused_dense = S->fused_dense && T.dense;
-      S->fused_nc = std::max(S->fused_nc, T.nc);
+    // the types with the dense form in one launch, the others in one of the general form
+    for (int dense = 1; dense >= 0; --dense) {
+      FusedLaunch& F = S->fused[dense];
+      std::vector<int> units;
+      for (int k : order) {
+        const TypeDev& T = S->types[k];
+        if (T.dense != (dense == 1)) continue;
+        const int epw = kTeam / T.team;
+        const int groups = (T.n_envs + epw - 1) / epw;
+        for (int g = 0; g < groups; ++g) units.insert(units.end(), {k, g});
+        F.lds = std::max(F.lds, T.lds_bytes);
+        F.nc = std::max(F.nc, T.nc);
+        F.team = T.team;
+      }
+      F.n_units = (int)(units.size() / 2);
+      if (F.n_units == 0) continue;
+      int per_cu = 0;
+      if (F.lds <= 160 * 1024 &&
+          (dense || F.lds <= 64 * 1024 || (err = set_fused_lds_limit(p->compute_fp64, F.team, F.lds)) == hipSuccess) &&
+          (err = dense ? dense_fused_blocks_per_cu(F.nc, p->solver == AGS_SOLVER_TGS, F.lds, &per_cu)
+                       : fused_blocks_per_cu(p->compute_fp64, F.team, F.lds, &per_cu)) == hipSuccess &&
+          (err = hipMalloc(&F.units, (units.size() + 1) * sizeof(int))) == hipSuccess &&
+          (err = hipMemcpy(F.units, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice)) == hipSuccess) {
+        F.grid = std::max(1, std::min(F.n_units, n_cu * std::max(1, per_cu)));
+      } else {
+        ags_sim_destroy(S);
+        return err != hipSuccess ? hip_fail(err, "sim: persistent launch set-up")
+                                 : fail(AGS_E_ARG, "sim: environment types too large for one persistent launch");
+      }
     }
-    for (int k : order) {
-      const TypeDev& T = S->types[k];
-      const int epw = kTeam / T.team;
-      const int groups = (T.n_envs + epw - 1) / epw;
-      for (int g = 0; g < groups; ++g) units.insert(units.end(), {k, g});
-      S->fused_lds = std::max(S->fused_lds, S->fused_dense ? T.lds_bytes : (size_t)T.lds.total * elem_size);
-    }
-    S->fused_team = S->types[0].team;
-    S->n_units = (int)(units.size() / 2);
-    int dev = 0, cus = 0, per_cu = 0;
-    if (S->fused_lds <= 160 * 1024 &&
-        (err = hipGetDevice(&dev)) == hipSuccess &&
-        (err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) == hipSuccess &&
-        (S->fused_lds <= 64 * 1024 || (err = set_fused_lds_limit(p->compute_fp64, S->fused_team, S->fused_lds)) == hipSuccess) &&
-        (err = S->fused_dense ? dense_fused_blocks_per_cu(S->fused_nc, p->solver == AGS_SOLVER_TGS, S->fused_lds, &per_cu)
-                              : fused_blocks_per_cu(p->compute_fp64, S->fused_team, S->fused_lds, &per_cu)) == hipSuccess &&
-        (err = hipMalloc(&S->units, (units.size() + 1) * sizeof(int))) == hipSuccess &&
-        (err = hipMemcpy(S->units, units.data(), units.size() * sizeof(int), hipMemcpyHostToDevice)) == hipSuccess) {
-      S->fused_grid = std::max(1, std::min(S->n_units, cus * std::max(1, per_cu)));
-      S->fused_ok = true;
-    } else {
-      ags_sim_destroy(S);
-      return err != hipSuccess ? hip_fail(err, "sim: persistent launch set-up")
-                               : fail(AGS_E_ARG, "sim: environment types too large for one persistent launch");
-    }
+    S->fused_ok = true;
   } else if (p->persistent) {
     ags_sim_destroy(S);
     return fail(AGS_E_ARG, "sim: a persistent launch takes at most 4 environment types");
@@ -956,7 +959,8 @@ extern "C" void ags_sim_destroy(ags_sim* S) {
   if (S->ev_big_listed) (void)hipEventDestroy(S->ev_big_listed);
   if (S->aux2) (void)hipStreamDestroy(S->aux2);
   if (S->env_tables) (void)hipFree(S->env_tables);
-  if (S->units) (void)hipFree(S->units);
+  for (FusedLaunch& F : S->fused)
+    if (F.units) (void)hipFree(F.units);
   if (S->kp_dof) (void)hipFree(S->kp_dof);
   if (S->actor_rows) (void)hipFree(S->actor_rows);
   delete S;
@@ -1059,13 +1063,18 @@ extern "C" int ags_sim_step(ags_sim* S, void* stream) {
     FusedArgs f{};
     f.base = a;
     for (size_t k = 0; k < S->types.size(); ++k) f.types[k] = type_args(S->types[k]);
-    f.units = S->units;
-    f.n_units = S->n_units;
-    f.taken = S->units + 2 * S->n_units;
-    hipError_t e = S->fused_dense ? launch_zero_count(f.taken, (hipStream_t)stream) : hipSuccess;
-    if (e == hipSuccess)
-      e = S->fused_dense ? launch_dense_fused(f, S->fused_nc, S->fused_grid, S->fused_lds, (hipStream_t)stream)
-                       : launch_step_fused(f, S->fused_grid, S->fused_lds, p.compute_fp64, S->fused_team, (hipStream_t)stream);
+    hipError_t e = hipSuccess;
+    for (int dense = 1; dense >= 0 && e == hipSuccess; --dense) {
+      const FusedLaunch& F = S->fused[dense];
+      if (F.n_units == 0) continue;
+      f.units = F.units;
+      f.n_units = F.n_units;
+      f.taken = F.units + 2 * F.n_units;
+      if (dense && (e = launch_zero_count(f.taken, (hipStream_t)stream)) == hipSuccess)
+        e = launch_dense_fused(f, F.nc, F.grid, F.lds, (hipStream_t)stream);
+      else if (!dense)
+        e = launch_step_fused(f, F.grid, F.lds, p.compute_fp64, F.team, (hipStream_t)stream);
+    }
     if (e != hipSuccess) return hip_fail(e, "step: launch");
     return AGS_OK;
   }
