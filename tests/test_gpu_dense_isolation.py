@@ -117,6 +117,21 @@ def test_non_finite_branch_of_a_fixed_base_stays_alone(lengths, what, value):
         check_alone(env, results(sim, env), range(n), parts, n)
 
 
+@pytest.mark.parametrize("env", [boxes(3), W.env_arm_box()], ids=lambda e: f"{e.name}{e.n_v}")
+def test_actor_without_orientation_stays_alone(env):
+    """A root quaternion of zeros (finite, but its unit quaternion is not)."""
+    env, p = W.as_f32(env), W.params_f32(W.SimParams())
+    parts, n = branches(env)
+    first = np.cumsum([0] + [len(a.links) for a in env.actors])
+    free = [a for a, actor in enumerate(env.actors) if actor.links[0].joint == "free"]
+    root, dof, act = states(env, p, len(free) + 1)
+    for e, a in enumerate(free, 1):
+        root[e, a, 3:7] = 0.0
+    sim = make(env, p, root, dof, act)
+    sim.step()
+    check_alone(env, results(sim, env), [parts[first[a]] for a in free], parts, n)
+
+
 @pytest.mark.parametrize("env", [forked(2, 2), forked(1, 2, 3), bare(W.env_arm_box())], ids=lambda e: f"{e.name}{e.n_v}")
 @pytest.mark.parametrize("solver", [0, 1], ids=["pgs", "tgs"])
 def test_massless_branch_stays_alone(env, solver):
