@@ -162,6 +162,7 @@ def test_massless_free_body_as_in_the_articulated_form(env, solver):
     mass = np.ones((len(free) + 1, env.n_bodies), np.float32)
     for e, k in enumerate(free, 1):
         mass[e, k] = 0.0
+        root[e, np.searchsorted(first, k, "right") - 1, 7:] += (0.3, -0.2, 0.1, 1.0, 2.0, -1.5)  # tumbling
     outs = []
     for lanes in (64, 32):
         sim = make(env, p, root, dof, act, lanes_per_env=lanes)
