@@ -856,11 +856,10 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
       }
       T.order_tmp = T.step_order + T.n_envs;
     }
-    // (1024: the streamed columns of A are read up to 13 rows past the matrix)
     const size_t elem = p->compute_fp64 ? sizeof(double) : sizeof(float);
     const int epw = kTeam / T.team;
     const size_t padded = (size_t)((T.n_envs + epw - 1) / epw) * epw;
-    if ((err = hipMalloc(&T.scratch, ((size_t)T.scratch_stride * padded + 1024) * elem)) != hipSuccess) {
+    if ((err = hipMalloc(&T.scratch, ((size_t)T.scratch_stride * padded + 64 * kRowsAhead) * elem)) != hipSuccess) {
       S->types.push_back(T);
       ags_sim_destroy(S);
       return hip_fail(err, "sim: scratch");

@@ -18,6 +18,8 @@ constexpr double kMinRootPivot = 1e-30;  // least pivot of a free root's inertia
 constexpr int kPhases = 10;           // controls, forward, inward, outward, v*, narrow, rows, responses, PGS, outputs
 constexpr int kJointEntries = 10;     // joint (non-root) entries of a compact Jacobian row
 constexpr int kFastRows = 32;         // rows solved in registers (one per lane); also the row-response chunk
+constexpr int kRowsAhead = 12;        // rows past the last that the sweeps over 33-64 streamed rows may read (not used): the
+                                      // scratch of a type ends with as many rows of the Delassus matrix
 
 // per-link integer table
 enum { LI_PARENT = 0, LI_JTYPE, LI_COL, LI_DOF, LI_ROOT, LI_CHILD_BEGIN, LI_CHILD_END, LI_ANC_BEGIN, LI_ANC_END,

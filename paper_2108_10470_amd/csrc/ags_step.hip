@@ -601,6 +601,7 @@ __device__ __forceinline__ void step_group(const StepArgs& P, const TypeArgs& T,
   constexpr int EPW = kTeam / TEAM;  // environments per wavefront
   constexpr int FR = kFastRows;      // rows of the register Gauss-Seidel path and of one response chunk
   constexpr int kWideAhead = 12;     // wide path: rows of A columns in flight ahead of the Gauss-Seidel updates
+  static_assert(kWideAhead <= kRowsAhead, "the last chunk stays inside the scratch");
   static_assert(FR <= TEAM, "fast rows exceed the lanes of an environment");
   const int t = threadIdx.x;         // lane in the wavefront
   const int tm = EPW == 1 ? 0 : t / TEAM;  // team (environment slot) of this lane
