@@ -516,6 +516,10 @@ struct TypeDev {
 
 int adj_fp64(const ags_sim_params& p) { return p.adjoint_precision == 64 || (p.adjoint_precision == 0 && p.compute_fp64); }
 
+// Rows of an env-step at most: the per-env limits tensor can bound joints that the model leaves free, so both limits of
+// every joint count (info.max_rows counts the model's own).
+int row_capacity(const ags_model_info& info) { return std::max(1, 2 * info.n_dof + 3 * info.n_slots); }
+
 Lds make_layout(const ags_model_info& info, int n_levels, int n_anc, int team, size_t elem) {
   Lds L{};
   int off = 0;
@@ -527,7 +531,7 @@ Lds make_layout(const ags_model_info& info, int n_levels, int n_anc, int team, s
   };
   auto take_i = [&](int ints) { return take((ints + ratio - 1) / ratio); };
   const int nl = info.n_links, na = info.n_actors, nd = info.n_dof, nv = info.n_v, ns = info.n_slots;
-  const int rc = std::max(1, info.max_rows);
+  const int rc = row_capacity(info);
   // integer model tables, shared by the environments of a workgroup
   L.t_li = take_i(nl * LI_COLS); L.t_lev = take_i(n_levels + 1); L.t_links = take_i(nl);
   L.t_child = take_i(nl); L.t_anc = take_i(n_anc); L.t_dof = take_i(nd); L.t_ai = take_i(na * AI_COLS);
@@ -776,7 +780,7 @@ extern "C" int ags_sim_create(const ags_model* const* models, int32_t n_models, 
     D.n_slots = M->info.n_slots;
     D.n_levels = M->n_levels;
     D.n_anc = M->n_anc;
-    D.r_cap = std::max(1, M->info.max_rows);
+    D.r_cap = row_capacity(M->info);
     D.n_body_slot = (int)M->body_slot.size();
     D.jfast = M->max_joint_entries <= kJointEntries;
     D.li = (const int*)(b + offs[0]);

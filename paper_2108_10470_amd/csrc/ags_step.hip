@@ -1593,7 +1593,7 @@ __device__ __forceinline__ void step_group(const StepArgs& P, const TypeArgs& T,
         const int keep = r < Rn && s.rinvA[r] != R(0);
         const unsigned long long m = team_ballot<TEAM>(tm, keep);
         const int pos = running + __popcll(m & lanes_below(tt));
-        if (keep && pos < M.r_cap) {
+        if (keep && pos < P.dbg_row_sub) {
           const int kr = s.rkr[r];
           const int kind = kr >> 16, ref = kr & 0xffff;
           const long long o = (long long)env * P.dbg_row_stride + (long long)sub_i * P.dbg_row_sub + pos;
